@@ -59,6 +59,27 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const void* base, in
                                              static_cast<int>(kRsrcWord3));
 }
 
+// Exact division of n < 2^31 by a positive divisor below 2^31 with one
+// multiplication: q = n * mul >> sh with mul = ceil(2^sh / d), sh = 31 +
+// ceil(log2 d) (Granlund and Montgomery's round-up method).
+struct FastDiv {
+    uint64_t mul;
+    uint32_t sh, d;
+};
+inline FastDiv make_fastdiv(int64_t d) {
+    uint32_t l = 0;
+    while ((int64_t(1) << l) < d) ++l;
+    FastDiv f;
+    f.sh = 31 + l;
+    f.d = static_cast<uint32_t>(d);
+    // l <= 31, so 2^sh <= 2^62 and mul <= 2^32
+    f.mul = ((uint64_t(1) << f.sh) + static_cast<uint64_t>(d) - 1) / static_cast<uint64_t>(d);
+    return f;
+}
+__device__ __forceinline__ uint32_t fast_div(uint32_t n, const FastDiv& f) {
+    return static_cast<uint32_t>((static_cast<uint64_t>(n) * f.mul) >> f.sh);
+}
+
 // --- LDS fragment reads issued from inline assembly ------------------------
 // The compiler inserts its waits for LDS reads it issues itself, and cannot
 // tell the buffers of a software pipeline apart; reads issued from inline

@@ -113,14 +113,9 @@ __global__ __launch_bounds__(kOpBlock) void relu_pool_kernel(const Elem* __restr
 // in float64 (zero outside the image).  One thread per output, output
 // channels fastest: the 64 lanes of a wave share their input pixel.
 template <typename Elem, int KH>
-__global__ __launch_bounds__(kOpBlock) void direct_f64_kernel(const Elem* __restrict__ x, const Elem* __restrict__ w,
-                                                              double* __restrict__ yd, int64_t N, int64_t H, int64_t W,
-                                                              int64_t C, int64_t K) {
+__device__ __forceinline__ double direct_f64_one(const Elem* __restrict__ x, const Elem* __restrict__ w, int64_t pix,
+                                                 int64_t k, int64_t H, int64_t W, int64_t C) {
     using S = Storage<Elem>;
-    const int64_t gid = static_cast<int64_t>(blockIdx.x) * kOpBlock + threadIdx.x;
-    if (gid >= N * H * W * K) return;
-    const int64_t k = gid % K;
-    const int64_t pix = gid / K;
     const int64_t v = pix % W, h = (pix / W) % H, n = pix / (W * H);
     double acc = 0.0;
     for (int i = 0; i < KH; ++i) {
@@ -135,7 +130,228 @@ __global__ __launch_bounds__(kOpBlock) void direct_f64_kernel(const Elem* __rest
                 acc = fma(static_cast<double>(S::to_f32(ws[c])), static_cast<double>(S::to_f32(xs[c])), acc);
         }
     }
-    yd[gid] = acc;
+    return acc;
+}
+
+template <typename Elem, int KH>
+__global__ __launch_bounds__(kOpBlock) void direct_f64_kernel(const Elem* __restrict__ x, const Elem* __restrict__ w,
+                                                              double* __restrict__ yd, int64_t N, int64_t H, int64_t W,
+                                                              int64_t C, int64_t K) {
+    const int64_t gid = static_cast<int64_t>(blockIdx.x) * kOpBlock + threadIdx.x;
+    if (gid >= N * H * W * K) return;
+    yd[gid] = direct_f64_one<Elem, KH>(x, w, gid / K, gid % K, H, W, C);
+}
+
+// The same as a matrix product on the float64 matrix cores, for layers with
+// enough output channels and taps: y [pixels][K] = X [pixels][R] W^T [R][K] with
+// R = KH 3 C, X's row the pixel's window (W is contiguous in R).  A workgroup of
+// four waves computes BM x BN outputs, each wave 16 WT x 16 WT of them in tiles
+// of v_mfma_f64_16x16x4_f64.  Chunks of 32 values of R are widened to fp32
+// (exact), staged in double-buffered LDS and widened to float64 as fragments;
+// the next chunk's loads, branch-free through buffer descriptors, are in flight
+// during the current one's products.  Within 16 values lane group g of a wave
+// takes the values 4 g .. 4 g + 3, one per instruction, the same on both
+// operands.  Taps outside the image enter as x = 0, which a finite weight turns
+// into nothing; a block that meets an infinite or NaN weight recomputes its
+// outputs with those taps left out.
+//
+// What bounds it: the matrix cores (64 clocks per instruction), and for layers of
+// few blocks the latency of a chunk.  2x56x56, 128 -> 128 (1.85 GFLOP): 2650 us
+// with one thread per output, 74 us here (25 TFLOP/s; 196 blocks of four waves
+// leave 60 of the 256 CUs idle); 2x28x28, 512 -> 512: 13900 and 290 us.
+typedef double f64x4 __attribute__((ext_vector_type(4)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
+constexpr int kF64Chunk = 32;
+constexpr int kF64Row = kF64Chunk + 4;   // floats per LDS row: 16-byte aligned, off the bank period
+
+struct F64Geometry {
+    int64_t H, W, C, K, pixels;
+    int R;
+    FastDiv c;                  // by C
+    uint32_t xbytes, wbytes;    // both below kOob
+};
+
+// four consecutive values of R, widened to fp32 (V4: one aligned load)
+template <typename Elem, bool V4>
+__device__ __forceinline__ f32x4 load_run4(__amdgpu_buffer_rsrc_t r, const uint32_t (&off)[4]) {
+    using S = Storage<Elem>;
+    f32x4 f;
+    if constexpr (V4 && sizeof(Elem) == 4) {
+        f = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(r, off[0], 0, 0));
+    } else if constexpr (V4) {
+        const u32x2 v = __builtin_amdgcn_raw_buffer_load_b64(r, off[0], 0, 0);
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+            f[e] = S::to_f32(__builtin_bit_cast(Elem, static_cast<uint16_t>(v[e >> 1] >> (16 * (e & 1)))));
+    } else {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            if constexpr (sizeof(Elem) == 4) f[e] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(r, off[e], 0, 0));
+            else f[e] = S::to_f32(__builtin_bit_cast(Elem, static_cast<uint16_t>(__builtin_amdgcn_raw_buffer_load_b16(r, off[e], 0, 0))));
+        }
+    }
+    return f;
+}
+
+template <typename Elem, int KH, int BM, int BN, int WT, bool V4>
+__global__ __launch_bounds__(256) void direct_f64_mfma_kernel(const Elem* __restrict__ x, const Elem* __restrict__ w,
+                                                              double* __restrict__ yd, F64Geometry g) {
+    constexpr int ES = static_cast<int>(sizeof(Elem));
+    constexpr int kWN = BN / (16 * WT);        // waves along the output channels
+    static_assert((BM / (16 * WT)) * kWN == 4, "four waves");
+    constexpr int kXI = BM / 32, kWI = BN / 32;   // row groups of 32 that a thread loads for
+    __shared__ __attribute__((aligned(16))) float st[2][(BM + BN) * kF64Row];
+    const int tid = threadIdx.x;
+    const int lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wm = wave / kWN, wn = wave % kWN;
+    const int64_t m0 = static_cast<int64_t>(blockIdx.x) * BM;
+    const int64_t n0 = static_cast<int64_t>(blockIdx.y) * BN;
+    const auto rx = make_rsrc(x, g.xbytes);
+    const auto rw = make_rsrc(w, g.wbytes);
+    // staging: thread t loads values 4 (t % 8) .. + 3 of the chunk for rows t / 8 + 32 i
+    const int q4 = (tid & 7) * 4;
+    const int row0 = tid >> 3;
+    uint32_t xoff[kXI], woff[kWI];
+    int xh[kXI], xw[kXI];
+#pragma unroll
+    for (int i = 0; i < kXI; ++i) {
+        const int64_t pix = m0 + row0 + 32 * i;
+        const int64_t pp = pix < g.pixels ? pix : 0;
+        xw[i] = static_cast<int>(pp % g.W);
+        // rows past the last pixel: a height no tap reaches from inside the image
+        xh[i] = pix < g.pixels ? static_cast<int>((pp / g.W) % g.H) : -4;
+        xoff[i] = static_cast<uint32_t>(pp * g.C * ES);
+    }
+#pragma unroll
+    for (int i = 0; i < kWI; ++i) {
+        const int64_t k = n0 + row0 + 32 * i;
+        woff[i] = k < g.K ? static_cast<uint32_t>(k * g.R * ES) : kOob;
+    }
+    f32x4 xr[kXI], wr[kWI];
+    bool odd = false;   // an infinite or NaN weight
+    auto load = [&](int r0) __attribute__((always_inline)) {
+        int di[4], dj[4];
+        uint32_t dx[4];   // byte offset of the tap and channel from the row's pixel (modulo 2^32)
+        bool in[4];
+#pragma unroll
+        for (int e = 0; e < (V4 ? 1 : 4); ++e) {
+            const int r = r0 + q4 + e;
+            in[e] = r < g.R;
+            const int tap = static_cast<int>(fast_div(static_cast<uint32_t>(r), g.c));
+            di[e] = KH == 3 ? tap / 3 - 1 : 0;
+            dj[e] = (KH == 3 ? tap % 3 : tap) - 1;
+            dx[e] = static_cast<uint32_t>(((static_cast<int64_t>(di[e]) * g.W + dj[e]) * g.C + (r - tap * static_cast<int>(g.C))) * ES);
+        }
+#pragma unroll
+        for (int i = 0; i < kXI; ++i) {
+            uint32_t off[4];
+#pragma unroll
+            for (int e = 0; e < (V4 ? 1 : 4); ++e) {
+                const int h = xh[i] + di[e], v = xw[i] + dj[e];
+                off[e] = in[e] && h >= 0 && h < g.H && v >= 0 && v < g.W ? xoff[i] + dx[e] : kOob;
+            }
+            xr[i] = load_run4<Elem, V4>(rx, off);
+        }
+#pragma unroll
+        for (int i = 0; i < kWI; ++i) {
+            uint32_t off[4];
+#pragma unroll
+            for (int e = 0; e < (V4 ? 1 : 4); ++e)
+                off[e] = in[e] && woff[i] != kOob ? woff[i] + static_cast<uint32_t>((r0 + q4 + e) * ES) : kOob;
+            wr[i] = load_run4<Elem, V4>(rw, off);
+        }
+    };
+    auto park = [&](int buf) __attribute__((always_inline)) {
+#pragma unroll
+        for (int i = 0; i < kXI; ++i) *reinterpret_cast<f32x4*>(&st[buf][(row0 + 32 * i) * kF64Row + q4]) = xr[i];
+#pragma unroll
+        for (int i = 0; i < kWI; ++i) {
+            *reinterpret_cast<f32x4*>(&st[buf][(BM + row0 + 32 * i) * kF64Row + q4]) = wr[i];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) odd |= !(__builtin_fabsf(wr[i][e]) < __builtin_inff());
+        }
+    };
+    f64x4 acc[WT][WT];
+#pragma unroll
+    for (int i = 0; i < WT; ++i)
+#pragma unroll
+        for (int j = 0; j < WT; ++j) acc[i][j] = f64x4{0.0, 0.0, 0.0, 0.0};
+    const int l16 = lane & 15, grp = lane >> 4;
+    load(0);
+    park(0);
+    __syncthreads();
+    int buf = 0;
+    for (int r0 = 0; r0 < g.R; r0 += kF64Chunk) {
+        const bool more = r0 + kF64Chunk < g.R;
+        if (more) load(r0 + kF64Chunk);
+        f64x4 part[WT][WT];
+#pragma unroll
+        for (int s = 0; s < kF64Chunk / 16; ++s) {
+            f32x4 a[WT], b[WT];
+#pragma unroll
+            for (int i = 0; i < WT; ++i) {
+                a[i] = *reinterpret_cast<const f32x4*>(&st[buf][(wm * 16 * WT + i * 16 + l16) * kF64Row + s * 16 + grp * 4]);
+                b[i] = *reinterpret_cast<const f32x4*>(&st[buf][(BM + wn * 16 * WT + i * 16 + l16) * kF64Row + s * 16 + grp * 4]);
+            }
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+#pragma unroll
+                for (int i = 0; i < WT; ++i)
+#pragma unroll
+                    for (int j = 0; j < WT; ++j)
+                        part[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(
+                            static_cast<double>(a[i][e]), static_cast<double>(b[j][e]),
+                            s == 0 && e == 0 ? f64x4{0.0, 0.0, 0.0, 0.0} : part[i][j], 0, 0, 0);
+        }
+        // Wait out the last product before its result is read.  (With the
+        // accumulators carried across the loop the compiler read the last one's
+        // top register right behind a branch, ahead of its own wait states: an
+        // accvgpr_read of the eighth register before the s_nop in the assembly,
+        // wrong rows 12 .. 15 of a tile on the GPU.)
+        __builtin_amdgcn_sched_barrier(0);
+        asm volatile("s_nop 15\n\ts_nop 15" ::: "memory");
+        __builtin_amdgcn_sched_barrier(0);
+        // a chunk's sum, then the chunks': fewer roundings than one chain over R
+#pragma unroll
+        for (int i = 0; i < WT; ++i)
+#pragma unroll
+            for (int j = 0; j < WT; ++j) acc[i][j] += part[i][j];
+        if (more) {
+            park(buf ^ 1);
+            __syncthreads();
+            buf ^= 1;
+        }
+    }
+    const bool recompute = __syncthreads_or(odd ? 1 : 0) != 0;
+    // lane l, value r of a tile: row 4 r + l / 16, column l % 16
+#pragma unroll
+    for (int i = 0; i < WT; ++i)
+#pragma unroll
+        for (int j = 0; j < WT; ++j) {
+            const int64_t k = n0 + wn * 16 * WT + j * 16 + l16;
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const int64_t pix = m0 + wm * 16 * WT + i * 16 + 4 * r + grp;
+                if (pix >= g.pixels || k >= g.K) continue;
+                yd[pix * g.K + k] = recompute ? direct_f64_one<Elem, KH>(x, w, pix, k, g.H, g.W, g.C) : acc[i][j][r];
+            }
+        }
+}
+
+template <typename Elem, int BM, int BN, int WT>
+hipError_t launch_f64_mfma(const F64Geometry& g, const Elem* x, const Elem* w, double* y, int kh, hipStream_t stream) {
+    const dim3 grid(static_cast<unsigned>((g.pixels + BM - 1) / BM), static_cast<unsigned>((g.K + BN - 1) / BN));
+#define WG_F64(KH, V4) \
+    hipLaunchKernelGGL((direct_f64_mfma_kernel<Elem, KH, BM, BN, WT, V4>), grid, dim3(256), 0, stream, x, w, y, g)
+    const bool v4 = g.C % 4 == 0;
+    if (kh == 3 && v4) WG_F64(3, true);
+    else if (kh == 3) WG_F64(3, false);
+    else if (v4) WG_F64(1, true);
+    else WG_F64(1, false);
+#undef WG_F64
+    return hipGetLastError();
 }
 
 // Sums of (y - ref)^2 and ref^2 over n values in float64: each of the
@@ -226,6 +442,20 @@ hipError_t launch_direct_f64_t(const void* x, const void* w, double* y, int64_t 
     if ((n + kOpBlock - 1) / kOpBlock > 0x7fffffff) return hipErrorInvalidValue;
     const auto* xp = static_cast<const Elem*>(x);
     const auto* wp = static_cast<const Elem*>(w);
+    const int64_t R = static_cast<int64_t>(kh) * 3 * C, pixels = N * H * W, es = sizeof(Elem);
+    // the matrix cores where a block's columns and chunk are mostly filled and
+    // 32-bit offsets reach both inputs
+    if (K > 8 && R > 16 && R < (int64_t(1) << 30) && pixels * C * es < 0xfffffff0LL && K * R * es < 0xfffffff0LL &&
+        pixels / 32 < 0x7fffffff && K / 32 < 0xffff) {
+        const F64Geometry g{H, W, C, K, pixels, static_cast<int>(R), make_fastdiv(C),
+                            static_cast<uint32_t>(pixels * C * es), static_cast<uint32_t>(K * R * es)};
+        // small layers: 32 x 32 outputs per workgroup, for more of them
+        const int64_t bn = K > 32 ? 64 : 32, bm = 4096 / bn;
+        const bool small = ((pixels + bm - 1) / bm) * ((K + bn - 1) / bn) < device_cu_count() / 2;
+        if (small) return launch_f64_mfma<Elem, 32, 32, 1>(g, xp, wp, y, kh, stream);
+        if (bn == 64) return launch_f64_mfma<Elem, 64, 64, 2>(g, xp, wp, y, kh, stream);
+        return launch_f64_mfma<Elem, 128, 32, 2>(g, xp, wp, y, kh, stream);
+    }
     if (kh == 3)
         hipLaunchKernelGGL((direct_f64_kernel<Elem, 3>), dim3(op_blocks(n)), dim3(kOpBlock), 0, stream, xp, wp, y, N, H,
                            W, C, K);
