@@ -630,6 +630,24 @@ wg_status winograd_conv1d(wg_plan plan, const wg_tensor* x, const wg_tensor* w, 
         default: e = wg::launch_kernel_transform_1d_t<2>(L.g, plan->ktab, w->data, U, stream); break;
     }
     if ((s = from_hip(e, "1D kernel transform")) != WG_OK) return s;
+    if (plan->channel_sum == WG_SUM_MFMA) {
+        bool fused = true;
+        switch (plan->dtype) {
+            case 0:
+                if ((fused = wg::conv1d_fused_chosen_t<0>(L.g)))
+                    e = wg::launch_conv1d_fused_t<0>(L.g, plan->itab, plan->otab, x->data, U, y->data, stream);
+                break;
+            case 1:
+                if ((fused = wg::conv1d_fused_chosen_t<1>(L.g)))
+                    e = wg::launch_conv1d_fused_t<1>(L.g, plan->itab, plan->otab, x->data, U, y->data, stream);
+                break;
+            default:
+                if ((fused = wg::conv1d_fused_chosen_t<2>(L.g)))
+                    e = wg::launch_conv1d_fused_t<2>(L.g, plan->itab, plan->otab, x->data, U, y->data, stream);
+                break;
+        }
+        if (fused) return from_hip(e, "1D transforms and contraction");
+    }
     switch (plan->dtype) {
         case 0: e = wg::launch_input_transform_1d_t<0>(L.g, plan->itab, x->data, V, stream); break;
         case 1: e = wg::launch_input_transform_1d_t<1>(L.g, plan->itab, x->data, V, stream); break;

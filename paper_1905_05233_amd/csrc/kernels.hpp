@@ -148,6 +148,13 @@ template <int D>
 hipError_t launch_output_transform_1d_t(const Geometry& g, const OutputTable& tab, const float* M, void* y,
                                         hipStream_t stream);
 
+// V, M and the output transform of the 1D form in one kernel: x and U -> y; the
+// layers for which it is taken.
+template <int D> bool conv1d_fused_chosen_t(const Geometry& g);
+template <int D>
+hipError_t launch_conv1d_fused_t(const Geometry& g, const InputTable& itab, const OutputTable& otab, const void* x,
+                                 const void* U, void* y, hipStream_t stream);
+
 // Compute units of the current device (cached per device).
 int device_cu_count();
 
