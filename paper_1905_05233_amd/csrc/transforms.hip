@@ -23,6 +23,7 @@
 #include "device_common.hpp"
 #include "input_regs.hpp"
 #include "kernels.hpp"
+#include "output_regs.hpp"
 
 #ifndef WG_DTYPE
 #error "compile with -DWG_DTYPE=0|1|2"
@@ -245,7 +246,8 @@ __global__ __launch_bounds__(kInBlock) void kernel_input_transform(
 // ----------------------------------------------------------------- output
 // y[n][ty*m+o][tx*m+p][k] = sum_b (sum_a A^T[o][a] M[a][b]) A^T[p][b]
 //
-// One workgroup per (tile, 64 output channels); the m output rows are split
+// For layers of few threads (others: output_regs.hpp).  One workgroup per (tile,
+// 64 output channels); the m output rows are split
 // over its waves (wave g computes rows [g*R, g*R + R) for its 64 channels).
 // Every wave loads the tile's alpha'^2 values of M for its channels, all
 // before any arithmetic (coalesced 256-byte rows; the repeats across the
@@ -256,6 +258,9 @@ constexpr int kOutCh = 64;   // output channels per workgroup, one per lane
 
 // rows per wave: the split that measured fastest
 constexpr int output_rows_per_wave(int alpha) { return alpha >= 9 ? 3 : 2; }
+
+// (tile, output channel) pairs from which the form of output_regs.hpp is taken
+constexpr int64_t kOutManyThreads = int64_t(1) << 17;
 
 template <int MM, int ALPHA>
 struct OutputShape {
@@ -456,6 +461,24 @@ hipError_t launch_in(const Geometry& g, const KernelTable* ktab, const InputTabl
 
 template <typename Elem, int TT, int A, class CO>
 hipError_t launch_ot(const Geometry& g, const OutputTable& tab, const float* M, Elem* yp, hipStream_t stream) {
+    if (g.T * g.K >= kOutManyThreads && g.T < (int64_t(1) << 31) && g.K < (int64_t(1) << 31)) {
+        // launches of whole tiles whose thread ids fit 31 bits (one but for huge layers)
+        OutputMap mp;
+        mp.per_tile = make_fastdiv(g.K);
+        mp.tw = make_fastdiv(g.tw);
+        mp.th = make_fastdiv(g.th);
+        const int64_t per = std::max<int64_t>(1, 0x7fffffff / g.K);
+        for (int64_t t0 = 0; t0 < g.T; t0 += per) {
+            mp.tile0 = t0;
+            mp.threads = std::min<int64_t>(per, g.T - t0) * g.K;
+            const int64_t blocks = (mp.threads + kOutBlock - 1) / kOutBlock * kOutGroups;
+            hipLaunchKernelGGL((output_transform_regs<Elem, TT - 2, A, CO>), dim3(static_cast<unsigned>(blocks)),
+                               dim3(kOutBlock), 0, stream, tab, M, yp, g, mp);
+            const hipError_t e = hipGetLastError();
+            if (e != hipSuccess) return e;
+        }
+        return hipSuccess;
+    }
     const int64_t units = g.T * ((g.K + kOutCh - 1) / kOutCh);
     if (units > 0x7fffffff) return hipErrorInvalidValue;
     hipLaunchKernelGGL((output_transform<Elem, TT - 2, A, CO>), dim3(static_cast<unsigned>(units)),
