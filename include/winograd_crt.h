@@ -275,6 +275,11 @@ wg_status winograd_conv2d_static(wg_plan plan, const wg_tensor* x, const wg_tens
 wg_status winograd_workspace_bytes_1d(wg_plan plan, int64_t N, int64_t L, int64_t C, int64_t K, size_t* bytes);
 wg_status winograd_conv1d(wg_plan plan, const wg_tensor* x, const wg_tensor* w, wg_tensor* y, hipStream_t stream);
 
+/* winograd_conv2d and winograd_conv1d with x, w and y as an array of three
+ * descriptors, for bindings to which building one buffer is cheaper. */
+wg_status winograd_conv2d_packed(wg_plan plan, const wg_tensor* xwy, hipStream_t stream);
+wg_status winograd_conv1d_packed(wg_plan plan, const wg_tensor* xwy, hipStream_t stream);
+
 /* ---- Stage entry points (each launches one kernel of winograd_conv2d) ----
  * Intermediate layouts, with Cp = C rounded up to a multiple of 8,
  * Kp = K rounded up to a multiple of 8, T = N * ceil(H/m) * ceil(W/m) tiles,

@@ -670,6 +670,20 @@ wg_status winograd_conv2d(wg_plan plan, const wg_tensor* x, const wg_tensor* w, 
     return conv2d_with(plan, x, w, y, plan->ws, plan->ws_bytes, false, stream);
 }
 
+wg_status winograd_conv2d_packed(wg_plan plan, const wg_tensor* xwy, hipStream_t stream) {
+    if (!plan) return fail(WG_ERR_ARG, "null plan");
+    if (!xwy) return fail(WG_ERR_ARG, "null tensor x");
+    wg_tensor y = xwy[2];
+    return conv2d_with(plan, &xwy[0], &xwy[1], &y, plan->ws, plan->ws_bytes, false, stream);
+}
+
+wg_status winograd_conv1d_packed(wg_plan plan, const wg_tensor* xwy, hipStream_t stream) {
+    if (!plan) return fail(WG_ERR_ARG, "null plan");
+    if (!xwy) return fail(WG_ERR_ARG, "null tensor x");
+    wg_tensor y = xwy[2];
+    return winograd_conv1d(plan, &xwy[0], &xwy[1], &y, stream);
+}
+
 wg_status winograd_conv2d_static(wg_plan plan, const wg_tensor* x, const wg_tensor* w, wg_tensor* y,
                                  hipStream_t stream) {
     if (!plan) return fail(WG_ERR_ARG, "null plan");

@@ -8,6 +8,7 @@ no CPU fallback: without the built library or a GPU the calls raise.
     y = plan.conv2d(x, w)          # x [N][H][W][C], w [K][3][3][C] -> y [N][H][W][K]
 """
 import ctypes
+import struct
 from fractions import Fraction
 
 import torch
@@ -15,6 +16,21 @@ import torch
 from . import _native as N
 
 TORCH_DTYPES = {"f32": torch.float32, "f16": torch.float16, "bf16": torch.bfloat16}
+# three wg_tensor descriptors (data, n, h, w, c) in one buffer
+_PACK3 = struct.Struct("P4qP4qP4q").pack
+_SIZES_KEPT = 256   # workspace sizes a plan remembers
+
+
+def _raw_stream(stream):
+    """The HIP stream as an integer: ``stream``'s, or the current one."""
+    if stream is not None:
+        return stream.cuda_stream
+    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+
+
+def _dense4(t, name):
+    if not (t.is_cuda and t.is_contiguous() and t.dim() == 4):
+        _tensor(t, name)   # raises
 
 
 def _stream_handle(stream):
@@ -76,6 +92,8 @@ class Plan:
         N.check(self._lib.winograd_plan_info(self._h, *[ctypes.byref(v) for v in vals]))
         self.m, self.r, self.alpha, self.tile_in, _ = [v.value for v in vals]
         self._ws = None
+        self._tdt = TORCH_DTYPES[dtype]
+        self._sizes = {}
 
     @classmethod
     def from_moduli(cls, moduli, m, dtype="f32", inner_points=None, inner_inf=True, r=3):
@@ -106,6 +124,8 @@ class Plan:
         N.check(self._lib.winograd_plan_info(self._h, *[ctypes.byref(v) for v in vals]))
         self.m, self.r, self.alpha, self.tile_in, _ = [v.value for v in vals]
         self._ws = None
+        self._tdt = TORCH_DTYPES[dtype]
+        self._sizes = {}
         return self
 
     # ------------------------------------------------------------ plan data
@@ -145,6 +165,17 @@ class Plan:
         N.check(self._lib.winograd_workspace_bytes(self._h, N_, H, W, C, K, ctypes.byref(out)))
         return out.value
 
+    def _need(self, sizes, query):
+        """Workspace bytes for a layer's sizes, asked of the library once per
+        plan and layer (they follow from the plan and the sizes alone)."""
+        need = self._sizes.get(sizes)
+        if need is None:
+            need = query(*sizes)
+            if len(self._sizes) >= _SIZES_KEPT:
+                self._sizes.clear()
+            self._sizes[sizes] = need
+        return need
+
     def conv_path(self, N_, H, W, C, K):
         """"separate", "fused" or "fused_input": the path conv2d takes for this layer shape."""
         out = ctypes.c_int()
@@ -174,23 +205,31 @@ class Plan:
 
     def conv2d(self, x, w, y=None, workspace=None, stream=None):
         """y = conv3x3(x, w), stride 1, padding 1 (NHWC), by eq. (2)."""
-        self._check_dtype(x, "x")
-        self._check_dtype(w, "w")
+        if x.dtype != self._tdt or w.dtype != self._tdt:
+            self._check_dtype(x, "x")
+            self._check_dtype(w, "w")
         Nn, H, W, C = x.shape
-        K = w.shape[0]
+        ws = w.shape
+        K = ws[0]
         if y is None:
-            y = torch.empty((Nn, H, W, K), dtype=x.dtype, device=x.device)
-        self._check_dtype(y, "y")
-        need = self.workspace_bytes(Nn, H, W, C, K)
+            y = x.new_empty((Nn, H, W, K))
+        else:
+            self._check_dtype(y, "y")
+        need = self._need((Nn, H, W, C, K), self.workspace_bytes)
         if workspace is None:
             if self._ws is None or self._ws.numel() < need or self._ws.device != x.device:
                 self.bind_workspace(torch.empty(need, dtype=torch.uint8, device=x.device))
         else:
             self.bind_workspace(workspace)
-        xt, wt, yt = _tensor(x, "x"), _tensor(w, "w"), _tensor(y, "y")
-        N.check(self._lib.winograd_conv2d(self._h, ctypes.byref(xt), ctypes.byref(wt), ctypes.byref(yt),
-                                          _stream_handle(stream)))
-        self._keep_for(stream, y)
+        _dense4(x, "x")
+        _dense4(w, "w")
+        _dense4(y, "y")
+        st = self._lib.winograd_conv2d_packed(
+            self._h, _PACK3(x.data_ptr(), Nn, H, W, C, w.data_ptr(), *ws, y.data_ptr(), *y.shape), _raw_stream(stream))
+        if st != N.WG_OK:
+            N.check(st)
+        if stream is not None:
+            self._keep_for(stream, y)
         return y
 
     def _keep_for(self, stream, y):
@@ -210,27 +249,34 @@ class Plan:
     def conv1d(self, x, w, y=None, workspace=None, stream=None):
         """1D F(m, 3): y [N][L][K] = conv(x [N][L][C], w [K][3][C]), stride 1,
         padding 1, along L (the descriptors carry height 1)."""
-        self._check_dtype(x, "x")
-        self._check_dtype(w, "w")
+        if x.dtype != self._tdt or w.dtype != self._tdt:
+            self._check_dtype(x, "x")
+            self._check_dtype(w, "w")
         if x.dim() != 3 or w.dim() != 3 or w.shape[1] != 3 or w.shape[2] != x.shape[2]:
             raise ValueError("x must be [N][L][C] and w [K][3][C]")
         Nn, L, C = x.shape
         K = w.shape[0]
         if y is None:
-            y = torch.empty((Nn, L, K), dtype=x.dtype, device=x.device)
-        self._check_dtype(y, "y")
-        need = self.workspace_bytes_1d(Nn, L, C, K)
+            y = x.new_empty((Nn, L, K))
+        else:
+            self._check_dtype(y, "y")
+        need = self._need((Nn, L, C, K), self.workspace_bytes_1d)
         if workspace is None:
             if self._ws is None or self._ws.numel() < need or self._ws.device != x.device:
                 self.bind_workspace(torch.empty(need, dtype=torch.uint8, device=x.device))
         else:
             self.bind_workspace(workspace)
-        xt = _tensor(x.unsqueeze(1), "x")
-        wt = _tensor(w.unsqueeze(1), "w")
-        yt = _tensor(y.unsqueeze(1), "y")
-        N.check(self._lib.winograd_conv1d(self._h, ctypes.byref(xt), ctypes.byref(wt), ctypes.byref(yt),
-                                          _stream_handle(stream)))
-        self._keep_for(stream, y)
+        for t, name in ((x, "x"), (w, "w"), (y, "y")):
+            if not (t.is_cuda and t.is_contiguous() and t.dim() == 3):
+                _tensor(t.unsqueeze(1), name)   # raises
+        yn, yl, yk = y.shape
+        st = self._lib.winograd_conv1d_packed(
+            self._h, _PACK3(x.data_ptr(), Nn, 1, L, C, w.data_ptr(), K, 1, 3, C, y.data_ptr(), yn, 1, yl, yk),
+            _raw_stream(stream))
+        if st != N.WG_OK:
+            N.check(st)
+        if stream is not None:
+            self._keep_for(stream, y)
         return y
 
     def conv2d_static(self, x, w, y, stream=None):
