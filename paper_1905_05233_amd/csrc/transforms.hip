@@ -42,7 +42,7 @@ constexpr int kBlock = 256;
 // it shares a launch with the input transform, to keep that kernel's register
 // count low).  kWhole: C is a multiple of the run, so the runs of w are
 // aligned; otherwise w is read element by element.
-constexpr int64_t kKtThreads = int64_t(1) << 16;
+constexpr int64_t kKtThreads = int64_t(1) << 15;
 template <int BYTES> struct RunBits;
 template <> struct RunBits<16> { using type = uint4; };
 template <> struct RunBits<8> { using type = uint2; };
@@ -419,7 +419,10 @@ hipError_t launch_in(const Geometry& g, const KernelTable* ktab, const InputTabl
             // the kernel transform's workgroups, a multiple of 8, so the input
             // transform's ids keep their XCD (id mod 8).  One thread for every
             // row a of a (k, 4-channel run) loads the taps once, but needs
-            // kKtThreads of them to cover the latency of its stores.
+            // kKtThreads of them to cover the latency of its stores: alpha' = 7
+            // in bf16 with next to no input, K x C = 256 x 256 (16 thousand
+            // threads) 5.2 us against 4.8 with a thread per row, 512 x 256 5.8
+            // against 6.1, 500 x 512 6.8 against 8.7.
             const int64_t kt_runs = g.K * (g.Cp / 4);
             const int kt_rows = kt_runs >= kKtThreads ? 1 : 0;
             const int64_t kt_thr = kt_rows ? kt_runs : kt_runs * A;
