@@ -240,6 +240,17 @@ wg_status winograd_plan_set_workspace(wg_plan plan, void* dev_ptr, size_t bytes)
 wg_status winograd_conv2d(wg_plan plan, const wg_tensor* x, const wg_tensor* w, wg_tensor* y,
                           hipStream_t stream);
 
+/* y = conv3x3(ReLU(x), w): the ReLU between two layers applied as the input
+ * transform reads x, so that it needs no pass over memory of its own.  The
+ * same bits as winograd_relu_pool (pool 0) followed by winograd_conv2d; same
+ * arguments, workspace and launches as winograd_conv2d.  WG_ERR_UNSUPPORTED,
+ * before anything is launched, where winograd_relu_input_supported reports 0:
+ * plans that are not built-in, WG_PATH_FUSED_INPUT, images over 1 GiB. */
+wg_status winograd_relu_input_supported(wg_plan plan, int64_t N, int64_t H, int64_t W, int64_t C, int64_t K,
+                                        int* supported);
+wg_status winograd_conv2d_relu_input(wg_plan plan, const wg_tensor* x, const wg_tensor* w, wg_tensor* y,
+                                     hipStream_t stream);
+
 /* Bytes of device workspace that winograd_conv2d_static has on each GPU. */
 #define WG_STATIC_SCRATCH_BYTES ((size_t)64 << 20)
 

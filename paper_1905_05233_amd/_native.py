@@ -86,6 +86,9 @@ def lib():
         "winograd_conv_chunks": (ctypes.c_int, [P, i64, i64, i64, i64, i64, ctypes.POINTER(i64), ctypes.POINTER(i64)]),
         "winograd_conv2d": (ctypes.c_int, [P, ctypes.POINTER(WgTensor), ctypes.POINTER(WgTensor),
                                            ctypes.POINTER(WgTensor), P]),
+        "winograd_relu_input_supported": (ctypes.c_int, [P, i64, i64, i64, i64, i64, ctypes.POINTER(ctypes.c_int)]),
+        "winograd_conv2d_relu_input": (ctypes.c_int, [P, ctypes.POINTER(WgTensor), ctypes.POINTER(WgTensor),
+                                                      ctypes.POINTER(WgTensor), P]),
         "winograd_conv2d_packed": (ctypes.c_int, [P, ctypes.c_char_p, P]),
         "winograd_conv1d_packed": (ctypes.c_int, [P, ctypes.c_char_p, P]),
         "winograd_workspace_bytes_1d": (ctypes.c_int, [P, i64, i64, i64, i64, ctypes.POINTER(sz)]),

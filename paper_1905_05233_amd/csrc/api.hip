@@ -265,19 +265,26 @@ hipError_t launch_kt(int dt, const wg::Geometry& g, const wg::KernelTable& t, co
     }
 }
 hipError_t launch_kit(int dt, const wg::Geometry& g, const wg::KernelTable& kt, const wg::InputTable& it,
-                      const void* w, const void* x, void* U, void* V, int bi, hipStream_t s) {
+                      const void* w, const void* x, void* U, void* V, int bi, hipStream_t s, bool relu = false) {
     switch (dt) {
-        case 0: return wg::launch_kernel_input_transform_t<0>(g, kt, it, w, x, U, V, bi, s);
-        case 1: return wg::launch_kernel_input_transform_t<1>(g, kt, it, w, x, U, V, bi, s);
-        default: return wg::launch_kernel_input_transform_t<2>(g, kt, it, w, x, U, V, bi, s);
+        case 0: return wg::launch_kernel_input_transform_t<0>(g, kt, it, w, x, U, V, bi, relu, s);
+        case 1: return wg::launch_kernel_input_transform_t<1>(g, kt, it, w, x, U, V, bi, relu, s);
+        default: return wg::launch_kernel_input_transform_t<2>(g, kt, it, w, x, U, V, bi, relu, s);
+    }
+}
+bool relu_input_supported(int dt, const wg::Geometry& g, int bi) {
+    switch (dt) {
+        case 0: return wg::input_relu_supported_t<0>(g, bi);
+        case 1: return wg::input_relu_supported_t<1>(g, bi);
+        default: return wg::input_relu_supported_t<2>(g, bi);
     }
 }
 hipError_t launch_it(int dt, const wg::Geometry& g, const wg::InputTable& t, const void* x, void* V, int bi,
-                     hipStream_t s) {
+                     hipStream_t s, bool relu = false) {
     switch (dt) {
-        case 0: return wg::launch_input_transform_t<0>(g, t, x, V, bi, s);
-        case 1: return wg::launch_input_transform_t<1>(g, t, x, V, bi, s);
-        default: return wg::launch_input_transform_t<2>(g, t, x, V, bi, s);
+        case 0: return wg::launch_input_transform_t<0>(g, t, x, V, bi, relu, s);
+        case 1: return wg::launch_input_transform_t<1>(g, t, x, V, bi, relu, s);
+        default: return wg::launch_input_transform_t<2>(g, t, x, V, bi, relu, s);
     }
 }
 hipError_t launch_ct(int dt, const wg::Geometry& g, const void* V, const void* U, float* M, hipStream_t s,
@@ -510,9 +517,9 @@ wg_status winograd_plan_set_workspace(wg_plan plan, void* dev_ptr, size_t bytes)
 namespace {
 
 // The launches of winograd_conv2d with the workspace at ws (ws_bytes long,
-// 256-byte aligned; nullptr: none) after the argument checks.
+// 256-byte aligned; nullptr: none) after the argument checks.  relu: of ReLU(x).
 wg_status conv2d_with(wg_plan plan, const wg_tensor* x, const wg_tensor* w, wg_tensor* y, void* ws,
-                      size_t ws_bytes, bool static_ws, hipStream_t stream) {
+                      size_t ws_bytes, bool static_ws, hipStream_t stream, bool relu = false) {
     wg_status s = check_plan(plan);
     if (s != WG_OK) return s;
     if ((s = check_tensor(x, "x")) != WG_OK || (s = check_tensor(w, "w")) != WG_OK ||
@@ -525,6 +532,8 @@ wg_status conv2d_with(wg_plan plan, const wg_tensor* x, const wg_tensor* w, wg_t
     if (!dims_ok(x->n, x->h, x->w, x->c, w->n)) return fail(WG_ERR_ARG, "layer sizes must be in [1, 2^31)");
     const Layout L = layout_for(plan, x->n, x->h, x->w, x->c, w->n);
     if (L.path < 0) return fail(WG_ERR_UNSUPPORTED, "the fused path does not support this layer shape");
+    if (relu && (L.path == WG_PATH_FUSED_INPUT || !relu_input_supported(plan->dtype, L.g, plan->builtin)))
+        return fail(WG_ERR_UNSUPPORTED, "ReLU of the input is not fused for this plan or layer shape");
     if (static_ws) {
         if (L.total > ws_bytes)
             return fail(WG_ERR_WORKSPACE, "layer needs " + std::to_string(L.total) +
@@ -555,9 +564,9 @@ wg_status conv2d_with(wg_plan plan, const wg_tensor* x, const wg_tensor* w, wg_t
             const wg::Geometry g = wg::make_geometry(nc, x->h, x->w, x->c, w->n, plan->tr.m, plan->tr.alpha);
             const void* xc = static_cast<const unsigned char*>(x->data) + n0 * x->h * x->w * x->c * es;
             void* yc = static_cast<unsigned char*>(y->data) + n0 * y->h * y->w * y->c * es;
-            s = n0 == 0 ? from_hip(launch_kit(dt, g, plan->ktab, plan->itab, w->data, xc, U, V, plan->builtin, stream),
+            s = n0 == 0 ? from_hip(launch_kit(dt, g, plan->ktab, plan->itab, w->data, xc, U, V, plan->builtin, stream, relu),
                                    "kernel and input transforms")
-                        : from_hip(launch_it(dt, g, plan->itab, xc, V, plan->builtin, stream), "input transform");
+                        : from_hip(launch_it(dt, g, plan->itab, xc, V, plan->builtin, stream, relu), "input transform");
             if (s != WG_OK) return s;
             if ((s = from_hip(launch_co(dt, g, plan->otab, V, U, yc, plan->builtin, stream), "fused contraction")) !=
                 WG_OK)
@@ -566,7 +575,7 @@ wg_status conv2d_with(wg_plan plan, const wg_tensor* x, const wg_tensor* w, wg_t
         }
         return WG_OK;
     }
-    s = from_hip(launch_kit(dt, L.g, plan->ktab, plan->itab, w->data, x->data, U, V, plan->builtin, stream),
+    s = from_hip(launch_kit(dt, L.g, plan->ktab, plan->itab, w->data, x->data, U, V, plan->builtin, stream, relu),
                  "kernel and input transforms");
     if (s != WG_OK) return s;
     if (L.path == WG_PATH_FUSED)
@@ -668,6 +677,22 @@ wg_status winograd_conv2d(wg_plan plan, const wg_tensor* x, const wg_tensor* w, 
                           hipStream_t stream) {
     if (!plan) return fail(WG_ERR_ARG, "null plan");
     return conv2d_with(plan, x, w, y, plan->ws, plan->ws_bytes, false, stream);
+}
+
+wg_status winograd_relu_input_supported(wg_plan plan, int64_t N, int64_t H, int64_t W, int64_t C, int64_t K,
+                                        int* supported) {
+    if (!plan || !supported) return fail(WG_ERR_ARG, "null argument");
+    if (!dims_ok(N, H, W, C, K)) return fail(WG_ERR_ARG, "layer sizes must be in [1, 2^31)");
+    const wg::Geometry g = wg::make_geometry(N, H, W, C, K, plan->tr.m, plan->tr.alpha);
+    const int path = resolve_path(plan, g);
+    *supported = path >= 0 && path != WG_PATH_FUSED_INPUT && relu_input_supported(plan->dtype, g, plan->builtin) ? 1 : 0;
+    return WG_OK;
+}
+
+wg_status winograd_conv2d_relu_input(wg_plan plan, const wg_tensor* x, const wg_tensor* w, wg_tensor* y,
+                                     hipStream_t stream) {
+    if (!plan) return fail(WG_ERR_ARG, "null plan");
+    return conv2d_with(plan, x, w, y, plan->ws, plan->ws_bytes, false, stream, true);
 }
 
 wg_status winograd_conv2d_packed(wg_plan plan, const wg_tensor* xwy, hipStream_t stream) {

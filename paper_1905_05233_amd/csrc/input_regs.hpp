@@ -93,8 +93,9 @@ template <typename Elem> struct InRun16 {
 template <> struct InRun<bf16_t, 1> : InRun16<bf16_t> {};
 template <> struct InRun<_Float16, 1> : InRun16<_Float16> {};
 
-// Both passes for the domain rows A0 .. A1-1.
-template <typename Elem, int TT, int ALPHA, class CO, int VEC, int A0, int A1>
+// Both passes for the domain rows A0 .. A1-1.  RELU: of ReLU(x), the elementwise
+// step between two layers, applied as the window is read.
+template <typename Elem, int TT, int ALPHA, class CO, int VEC, bool RELU, int A0, int A1>
 __device__ __forceinline__ void input_regs_rows(const InputTable& tab, const typename InRun<Elem, VEC>::Bits (&d)[TT][TT],
                                                 unsigned char* out, uint32_t lo, int64_t plane) {
     using R = InRun<Elem, VEC>;
@@ -105,7 +106,13 @@ __device__ __forceinline__ void input_regs_rows(const InputTable& tab, const typ
     for (int v = 0; v < TT; ++v) {
         float col[TT][VEC];
 #pragma unroll
-        for (int u = 0; u < TT; ++u) R::unpack(d[v][u], col[u]);
+        for (int u = 0; u < TT; ++u) {
+            R::unpack(d[v][u], col[u]);
+            if constexpr (RELU) {
+#pragma unroll
+                for (int q = 0; q < VEC; ++q) col[u][q] = col[u][q] > 0.0f ? col[u][q] : 0.0f;   // NaN and -0 give +0
+            }
+        }
 #pragma unroll
         for (int a = 0; a < NR; ++a)
 #pragma unroll
@@ -131,14 +138,14 @@ __device__ __forceinline__ void input_regs_rows(const InputTable& tab, const typ
             *reinterpret_cast<Bits*>(out + ((A0 + a) * ALPHA + b) * plane + lo) = R::pack(f);
         }
 }
-template <typename Elem, int TT, int ALPHA, class CO, int VEC, int kR, int... Gs>
+template <typename Elem, int TT, int ALPHA, class CO, int VEC, bool RELU, int kR, int... Gs>
 __device__ __forceinline__ void input_regs_groups(const InputTable& tab, const typename InRun<Elem, VEC>::Bits (&d)[TT][TT],
                                                   unsigned char* out, uint32_t lo, int64_t plane, int g,
                                                   std::integer_sequence<int, Gs...>) {
     auto one = [&](auto gc) __attribute__((always_inline)) {
         constexpr int a0 = decltype(gc)::value * kR, a1 = a0 + kR < ALPHA ? a0 + kR : ALPHA;
         if constexpr (a0 < a1)
-            if (g == decltype(gc)::value) input_regs_rows<Elem, TT, ALPHA, CO, VEC, a0, a1>(tab, d, out, lo, plane);
+            if (g == decltype(gc)::value) input_regs_rows<Elem, TT, ALPHA, CO, VEC, RELU, a0, a1>(tab, d, out, lo, plane);
     };
     (one(std::integral_constant<int, Gs>{}), ...);
 }
@@ -200,7 +207,7 @@ __device__ __forceinline__ void input_window_big(const Elem* __restrict__ x, con
         }
 }
 
-template <typename Elem, int TT, int ALPHA, class CO, int VEC, int RG, bool BIG>
+template <typename Elem, int TT, int ALPHA, class CO, int VEC, int RG, bool BIG, bool RELU>
 __device__ __forceinline__ void input_regs_unit(const InputTable& tab, const Elem* __restrict__ x,
                                                 unsigned char* __restrict__ V, const Geometry& geo,
                                                 const InputMap& mp, int64_t bid, int64_t G) {
@@ -222,10 +229,10 @@ __device__ __forceinline__ void input_regs_unit(const InputTable& tab, const Ele
     unsigned char* out = V + base * (VEC * ES);
     const uint32_t lo = threadIdx.x * (VEC * ES);
     if constexpr (RG == 1) {
-        input_regs_rows<Elem, TT, ALPHA, CO, VEC, 0, ALPHA>(tab, d, out, lo, mp.plane);
+        input_regs_rows<Elem, TT, ALPHA, CO, VEC, RELU, 0, ALPHA>(tab, d, out, lo, mp.plane);
     } else {
         constexpr int kR = (ALPHA + RG - 1) / RG;
-        input_regs_groups<Elem, TT, ALPHA, CO, VEC, kR>(tab, d, out, lo, mp.plane, group,
+        input_regs_groups<Elem, TT, ALPHA, CO, VEC, RELU, kR>(tab, d, out, lo, mp.plane, group,
                                                         std::make_integer_sequence<int, RG>{});
     }
 }

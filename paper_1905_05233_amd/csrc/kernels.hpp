@@ -84,14 +84,16 @@ template <int D>
 hipError_t launch_kernel_transform_t(const Geometry& g, const KernelTable& tab, const void* w, void* U,
                                      hipStream_t stream);
 // builtin: the id of a built-in plan whose tables the plan has (its
-// constant-coefficient kernels are used), or -1.
+// constant-coefficient kernels are used), or -1.  relu: the transform of
+// ReLU(x), where input_relu_supported_t says so (built-in plans).
+template <int D> bool input_relu_supported_t(const Geometry& g, int builtin);
 template <int D>
 hipError_t launch_input_transform_t(const Geometry& g, const InputTable& tab, const void* x, void* V, int builtin,
-                                    hipStream_t stream);
+                                    bool relu, hipStream_t stream);
 // Both transforms in one launch (they are independent): U from w and V from x.
 template <int D>
 hipError_t launch_kernel_input_transform_t(const Geometry& g, const KernelTable& ktab, const InputTable& itab,
-                                           const void* w, const void* x, void* U, void* V, int builtin,
+                                           const void* w, const void* x, void* U, void* V, int builtin, bool relu,
                                            hipStream_t stream);
 template <int D>
 hipError_t launch_output_transform_t(const Geometry& g, const OutputTable& tab, const float* M, void* y,

@@ -215,10 +215,10 @@ constexpr int kInGroups = 4;
 constexpr int64_t kInFewThreads = int64_t(1) << 15;
 constexpr int input_groups(int tt) { return tt >= 8 ? kInGroups : 1; }
 
-template <typename Elem, int TT, int ALPHA, class CO, int VEC, int RG, bool BIG>
+template <typename Elem, int TT, int ALPHA, class CO, int VEC, int RG, bool BIG, bool RELU>
 __global__ __launch_bounds__(kInBlock) void input_transform(InputTable tab, const Elem* __restrict__ x,
                                                             unsigned char* __restrict__ V, Geometry geo, InputMap mp) {
-    input_regs_unit<Elem, TT, ALPHA, CO, VEC, RG, BIG>(tab, x, V, geo, mp, blockIdx.x, gridDim.x);
+    input_regs_unit<Elem, TT, ALPHA, CO, VEC, RG, BIG, RELU>(tab, x, V, geo, mp, blockIdx.x, gridDim.x);
 }
 
 // The kernel and input transforms are independent: conv2d runs them as one
@@ -227,7 +227,7 @@ __global__ __launch_bounds__(kInBlock) void input_transform(InputTable tab, cons
 // transform overlaps the input transform).  kt_rows: one kernel-transform
 // thread per (k, 4-channel run) for every row a, else one per row; whole: C is a
 // multiple of 16 bytes, so the runs of w are aligned.
-template <typename Elem, int TT, int ALPHA, class CO, int VEC, int RG>
+template <typename Elem, int TT, int ALPHA, class CO, int VEC, int RG, bool RELU>
 __global__ __launch_bounds__(kInBlock) void kernel_input_transform(
     KernelTable ktab, InputTable itab, const Elem* __restrict__ w, const Elem* __restrict__ x,
     Elem* __restrict__ U, unsigned char* __restrict__ V, Geometry geo, InputMap mp, KernelMap kmp, int64_t n_kt, int kt_rows, int whole) {
@@ -240,7 +240,7 @@ __global__ __launch_bounds__(kInBlock) void kernel_input_transform(
         else kernel_transform_run<Elem, ALPHA, 4, false>(ktab, w, U, geo.K, geo.C, geo.Cp, kmp, gid);
         return;
     }
-    input_regs_unit<Elem, TT, ALPHA, CO, VEC, RG, false>(itab, x, V, geo, mp, bid - n_kt, gridDim.x - n_kt);
+    input_regs_unit<Elem, TT, ALPHA, CO, VEC, RG, false, RELU>(itab, x, V, geo, mp, bid - n_kt, gridDim.x - n_kt);
 }
 
 // ----------------------------------------------------------------- output
@@ -374,9 +374,9 @@ hipError_t launch_kernel_transform_t(const Geometry& g, const KernelTable& tab, 
 
 // One launch of each kernel shape, with the coefficient source CO.  The images
 // go in groups whose bytes and threads fit 32-bit arithmetic (one group but for
-// inputs over 1 GiB); kt_first: the first group's launch carries the kernel
-// transform.
-template <typename Elem, int TT, int A, class CO>
+// inputs over 1 GiB); with ktab the first group's launch carries the kernel
+// transform.  RELU: of ReLU(x) (images within one launch's reach).
+template <typename Elem, int TT, int A, class CO, bool RELU = false>
 hipError_t launch_in(const Geometry& g, const KernelTable* ktab, const InputTable& tab, const Elem* wp, const Elem* xp,
                      Elem* up, Elem* vp, hipStream_t stream) {
     constexpr int ES = static_cast<int>(sizeof(Elem));
@@ -391,6 +391,7 @@ hipError_t launch_in(const Geometry& g, const KernelTable* ktab, const InputTabl
     mp.th = make_fastdiv(g.th);
     mp.plane = g.T * g.Cp * ES;
     const bool big = x_img * ES > kInMaxBytes || thr_img > 0x7fffffff;
+    if (big && RELU) return hipErrorInvalidValue;
     if (big) {
         // larger images: the kernel transform apart, 64-bit addresses
         mp.threads = g.T * g.Cp;
@@ -402,7 +403,7 @@ hipError_t launch_in(const Geometry& g, const KernelTable* ktab, const InputTabl
             const hipError_t e = launch_kernel_transform_t<D>(g, *ktab, wp, up, stream);
             if (e != hipSuccess) return e;
         }
-        hipLaunchKernelGGL((input_transform<Elem, TT, A, RuntimeCoefs, 1, 1, true>), dim3(static_cast<unsigned>(blocks)),
+        hipLaunchKernelGGL((input_transform<Elem, TT, A, RuntimeCoefs, 1, 1, true, false>), dim3(static_cast<unsigned>(blocks)),
                            dim3(kInBlock), 0, stream, tab, xp, reinterpret_cast<unsigned char*>(vp), g, mp);
         return hipGetLastError();
     }
@@ -432,7 +433,7 @@ hipError_t launch_in(const Geometry& g, const KernelTable* ktab, const InputTabl
             const dim3 grid(static_cast<unsigned>(n_kt + units));
             const int whole = g.C % (16 / ES) == 0 ? 1 : 0;
 #define WG_KIT(VEC, RG)                                                                                           \
-    hipLaunchKernelGGL((kernel_input_transform<Elem, TT, A, CO, VEC, RG>), grid, dim3(kInBlock), 0, stream, *ktab, \
+    hipLaunchKernelGGL((kernel_input_transform<Elem, TT, A, CO, VEC, RG, RELU>), grid, dim3(kInBlock), 0, stream, *ktab, \
                        tab, wp, xs, up, vs, g, mp, kmp, n_kt, kt_rows, whole)
             if constexpr (kPairs) {
                 if (pairs) WG_KIT(2, 1);
@@ -446,7 +447,7 @@ hipError_t launch_in(const Geometry& g, const KernelTable* ktab, const InputTabl
             if (units > 0x7fffffff) return hipErrorInvalidValue;
             const dim3 grid(static_cast<unsigned>(units));
 #define WG_IT(VEC, RG) \
-    hipLaunchKernelGGL((input_transform<Elem, TT, A, CO, VEC, RG, false>), grid, dim3(kInBlock), 0, stream, tab, xs, vs, g, mp)
+    hipLaunchKernelGGL((input_transform<Elem, TT, A, CO, VEC, RG, false, RELU>), grid, dim3(kInBlock), 0, stream, tab, xs, vs, g, mp)
             if constexpr (kPairs) {
                 if (pairs) WG_IT(2, 1);
                 else WG_IT(1, 1);
@@ -492,11 +493,29 @@ hipError_t launch_ot(const Geometry& g, const OutputTable& tab, const float* M, 
 // Dispatch: the constant-coefficient instance of a built-in plan (builtin =
 // its id, when the shape matches), else the kernel-argument tables.
 template <int D>
+bool input_relu_supported_t(const Geometry& g, int builtin) {
+    return builtin >= 0 && g.t <= 8 && g.H * g.W * g.C * dtype_bytes(D) <= kInMaxBytes &&
+           g.th * g.tw * g.Cp <= 0x7fffffff;
+}
+
+template <int D>
 hipError_t launch_input_transform_t(const Geometry& g, const InputTable& tab, const void* x, void* V,
-                                    int builtin, hipStream_t stream) {
+                                    int builtin, bool relu, hipStream_t stream) {
     using Elem = typename DTypeOf<D>::type;
     const auto* xp = static_cast<const Elem*>(x);
     auto* vp = static_cast<Elem*>(V);
+    if (relu && !input_relu_supported_t<D>(g, builtin)) return hipErrorInvalidValue;
+    if (relu) {
+        switch (builtin) {
+#define WG_IT_RELU(ID, TT, A)                                                                              \
+    case ID:                                                                                               \
+        return launch_in<Elem, TT, A, ConstCoefs<BuiltinPlan##ID>, true>(g, nullptr, tab, nullptr, xp, nullptr, vp, stream);
+            WG_BUILTIN_PLANS(WG_IT_RELU)
+#undef WG_IT_RELU
+            default:
+                return hipErrorInvalidValue;
+        }
+    }
     switch (builtin) {
 #define WG_IT_BUILTIN(ID, TT, A)                                                                           \
     case ID:                                                                                               \
@@ -519,7 +538,7 @@ hipError_t launch_input_transform_t(const Geometry& g, const InputTable& tab, co
 
 template <int D>
 hipError_t launch_kernel_input_transform_t(const Geometry& g, const KernelTable& ktab, const InputTable& itab,
-                                           const void* w, const void* x, void* U, void* V, int builtin,
+                                           const void* w, const void* x, void* U, void* V, int builtin, bool relu,
                                            hipStream_t stream) {
     using Elem = typename DTypeOf<D>::type;
     const auto* wp = static_cast<const Elem*>(w);
@@ -528,7 +547,19 @@ hipError_t launch_kernel_input_transform_t(const Geometry& g, const KernelTable&
     auto* vp = static_cast<Elem*>(V);
     if (g.t > 8) {   // larger tiles: two launches (a combined kernel is large and saves little)
         const hipError_t e = launch_kernel_transform_t<D>(g, ktab, w, U, stream);
-        return e != hipSuccess ? e : launch_input_transform_t<D>(g, itab, x, V, builtin, stream);
+        return e != hipSuccess ? e : launch_input_transform_t<D>(g, itab, x, V, builtin, relu, stream);
+    }
+    if (relu && !input_relu_supported_t<D>(g, builtin)) return hipErrorInvalidValue;
+    if (relu) {
+        switch (builtin) {
+#define WG_KIT_RELU(ID, TT, A)                                                                             \
+    case ID:                                                                                               \
+        return launch_in<Elem, TT, A, ConstCoefs<BuiltinPlan##ID>, true>(g, &ktab, itab, wp, xp, up, vp, stream);
+            WG_BUILTIN_PLANS(WG_KIT_RELU)
+#undef WG_KIT_RELU
+            default:
+                return hipErrorInvalidValue;
+        }
     }
     switch (builtin) {
 #define WG_KIT_BUILTIN(ID, TT, A)                                                                          \
@@ -576,11 +607,12 @@ hipError_t launch_output_transform_t(const Geometry& g, const OutputTable& tab, 
 
 template hipError_t launch_kernel_transform_t<WG_DTYPE>(const Geometry&, const KernelTable&, const void*, void*,
                                                         hipStream_t);
+template bool input_relu_supported_t<WG_DTYPE>(const Geometry&, int);
 template hipError_t launch_input_transform_t<WG_DTYPE>(const Geometry&, const InputTable&, const void*, void*, int,
-                                                       hipStream_t);
+                                                       bool, hipStream_t);
 template hipError_t launch_kernel_input_transform_t<WG_DTYPE>(const Geometry&, const KernelTable&,
                                                               const InputTable&, const void*, const void*, void*,
-                                                              void*, int, hipStream_t);
+                                                              void*, int, bool, hipStream_t);
 template hipError_t launch_output_transform_t<WG_DTYPE>(const Geometry&, const OutputTable&, const float*, void*,
                                                         int, hipStream_t);
 

@@ -232,6 +232,28 @@ class Plan:
             self._keep_for(stream, y)
         return y
 
+    def relu_input_supported(self, N_, H, W, C, K):
+        """Whether conv2d_relu_input takes this layer."""
+        out = ctypes.c_int()
+        N.check(self._lib.winograd_relu_input_supported(self._h, N_, H, W, C, K, ctypes.byref(out)))
+        return bool(out.value)
+
+    def conv2d_relu_input(self, x, w):
+        """conv2d of ReLU(x): the same bits as conv2d(relu_pool(x, False), w)
+        with the ReLU applied as the input transform reads x."""
+        self._check_dtype(x, "x")
+        self._check_dtype(w, "w")
+        Nn, H, W, C = x.shape
+        K = w.shape[0]
+        y = x.new_empty((Nn, H, W, K))
+        need = self._need((Nn, H, W, C, K), self.workspace_bytes)
+        if self._ws is None or self._ws.numel() < need or self._ws.device != x.device:
+            self.bind_workspace(torch.empty(need, dtype=torch.uint8, device=x.device))
+        xt, wt, yt = _tensor(x, "x"), _tensor(w, "w"), _tensor(y, "y")
+        N.check(self._lib.winograd_conv2d_relu_input(self._h, ctypes.byref(xt), ctypes.byref(wt), ctypes.byref(yt),
+                                                     _raw_stream(None)))
+        return y
+
     def _keep_for(self, stream, y):
         """Memory allocated here on the current stream but used on another
         one: keep the caching allocator from reusing it before that stream's
