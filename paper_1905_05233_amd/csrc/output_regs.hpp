@@ -6,6 +6,14 @@
 // ascending, fp32 fused multiply-adds from zero, rounded once at the store.  A
 // domain column at a time: its alpha' values of M are loaded, folded into Z[o]
 // and those into the m x m outputs.
+//
+// What bounds it: alpha'^2 / m^2 times the fp32 bytes of the output are read.  A
+// workgroup's threads span consecutive (tile, channel) pairs, so none is idle
+// where K is not a multiple of 64, and two row groups read M twice (the second
+// time from the caches) instead of once per wave of up to four.  Against one
+// workgroup per (tile, 64 channels): 6x75x91x120 in fp16 17.4 -> 12.3 us,
+// 32x28x28x512 in bf16 28.0 -> 26.7 us (157 MB of M, 5.9 TB/s), 16x60x60x128 with
+// 10x10 windows in fp32 42.6 -> 25.3 us.
 #pragma once
 
 #include "coefs.hpp"

@@ -201,8 +201,8 @@ __global__ __launch_bounds__(kBlock) void kernel_transform(KernelTable tab, cons
 // The input transform itself is in input_regs.hpp.
 
 // Channels per thread: pairs (4-byte accesses) in 16-bit storage where the
-// window's registers allow it and C is even, so that no run straddles two
-// pixels.  With windows read from HBM pairs measured 53 against 57 us for
+// window's registers allow it, C is even, so that no run straddles two pixels,
+// and the layer has threads enough (kInFirstUnits).  With windows read from HBM pairs measured 53 against 57 us for
 // 32x56x56x256; from 8x8 windows on their registers halve the waves in flight
 // (9.2 against 8.2 us for 16x28x28x256, alpha' = 10).
 template <typename Elem> constexpr bool input_pairs(int tt) { return sizeof(Elem) == 2 && tt <= 6; }
@@ -213,6 +213,14 @@ template <typename Elem> constexpr bool input_pairs(int tt) { return sizeof(Elem
 // us, while 16x28x28x256 with 6x6 tiles (102 thousand) went from 8.1 to 9.4 us.
 constexpr int kInGroups = 4;
 constexpr int64_t kInFewThreads = int64_t(1) << 15;
+// Layers of at most one workgroup of one-channel threads per CU are bound by one
+// thread's latency: they take one channel per thread, and in the joint launch
+// their units go ahead of the kernel transform, so that they don't start last.
+// The joint launch, F(4x4) with a^2+1 in bf16, pairs behind the kernel transform
+// -> pairs ahead -> single channels ahead: 1x14x14, 512 -> 512 7.71 -> 7.33 -> 7.07 us,
+// 1x28x28, 256 -> 256 5.15 -> 4.99 -> 4.33, 4x14x14, 512 -> 32 4.79 -> 4.42 -> 3.74.
+// With more units the short kernel transform stays ahead.
+constexpr int64_t kInFirstUnits = 256;
 constexpr int input_groups(int tt) { return tt >= 8 ? kInGroups : 1; }
 
 template <typename Elem, int TT, int ALPHA, class CO, int VEC, int RG, bool BIG, bool RELU>
@@ -222,25 +230,27 @@ __global__ __launch_bounds__(kInBlock) void input_transform(InputTable tab, cons
 }
 
 // The kernel and input transforms are independent: conv2d runs them as one
-// launch.  The first n_kt workgroups run the kernel transform, the rest are
+// launch.  n_kt workgroups run the kernel transform, the rest are
 // input-transform units (one launch instead of two, and the short kernel
-// transform overlaps the input transform).  kt_rows: one kernel-transform
+// transform overlaps the input transform); n_first units (all or none) go
+// ahead of the kernel transform.  kt_rows: one kernel-transform
 // thread per (k, 4-channel run) for every row a, else one per row; whole: C is a
 // multiple of 16 bytes, so the runs of w are aligned.
 template <typename Elem, int TT, int ALPHA, class CO, int VEC, int RG, bool RELU>
 __global__ __launch_bounds__(kInBlock) void kernel_input_transform(
     KernelTable ktab, InputTable itab, const Elem* __restrict__ w, const Elem* __restrict__ x,
-    Elem* __restrict__ U, unsigned char* __restrict__ V, Geometry geo, InputMap mp, KernelMap kmp, int64_t n_kt, int kt_rows, int whole) {
+    Elem* __restrict__ U, unsigned char* __restrict__ V, Geometry geo, InputMap mp, KernelMap kmp, int64_t n_kt, int64_t n_first,
+    int kt_rows, int whole) {
     const int64_t bid = blockIdx.x;
-    if (bid < n_kt) {
-        const int64_t gid = bid * kInBlock + threadIdx.x;
+    if (bid >= n_first && bid < n_first + n_kt) {
+        const int64_t gid = (bid - n_first) * kInBlock + threadIdx.x;
         if (kt_rows && whole) kernel_transform_rows<Elem, ALPHA, 4, true>(ktab, w, U, geo.K, geo.C, geo.Cp, kmp, gid);
         else if (kt_rows) kernel_transform_rows<Elem, ALPHA, 4, false>(ktab, w, U, geo.K, geo.C, geo.Cp, kmp, gid);
         else if (whole) kernel_transform_run<Elem, ALPHA, 4, true>(ktab, w, U, geo.K, geo.C, geo.Cp, kmp, gid);
         else kernel_transform_run<Elem, ALPHA, 4, false>(ktab, w, U, geo.K, geo.C, geo.Cp, kmp, gid);
         return;
     }
-    input_regs_unit<Elem, TT, ALPHA, CO, VEC, RG, false, RELU>(itab, x, V, geo, mp, bid - n_kt, gridDim.x - n_kt);
+    input_regs_unit<Elem, TT, ALPHA, CO, VEC, RG, false, RELU>(itab, x, V, geo, mp, bid < n_first ? bid : bid - n_kt, gridDim.x - n_kt);
 }
 
 // ----------------------------------------------------------------- output
@@ -259,7 +269,10 @@ constexpr int kOutCh = 64;   // output channels per workgroup, one per lane
 // rows per wave: the split that measured fastest
 constexpr int output_rows_per_wave(int alpha) { return alpha >= 9 ? 3 : 2; }
 
-// (tile, output channel) pairs from which the form of output_regs.hpp is taken
+// (tile, output channel) pairs from which the form of output_regs.hpp is taken: it
+// has fewer waves, which layers of fewer pairs need to hide the loads of M
+// (1x14x14x512 in bf16 has 8 thousand; 6x75x91x120 in fp16, 315 thousand, 17.4 us
+// here and 12.3 there; 32x28x28x512 28.0 and 26.7).
 constexpr int64_t kOutManyThreads = int64_t(1) << 17;
 
 template <int MM, int ALPHA>
@@ -382,7 +395,8 @@ hipError_t launch_in(const Geometry& g, const KernelTable* ktab, const InputTabl
     constexpr int ES = static_cast<int>(sizeof(Elem));
     constexpr bool kPairs = input_pairs<Elem>(TT);
     constexpr int kRG = input_groups(TT);
-    const bool pairs = kPairs && g.C % 2 == 0;
+    const bool few = g.T * g.Cp <= kInFirstUnits * kInBlock;
+    const bool pairs = kPairs && g.C % 2 == 0 && !few;
     const int vec = pairs ? 2 : 1;
     const int64_t tiles_img = g.th * g.tw, thr_img = tiles_img * (g.Cp / vec), x_img = g.H * g.W * g.C;
     InputMap mp;
@@ -431,10 +445,11 @@ hipError_t launch_in(const Geometry& g, const KernelTable* ktab, const InputTabl
             const int64_t n_kt = (kt_thr + 8 * kInBlock - 1) / (8 * kInBlock) * 8;
             if (n_kt + units > 0x7fffffff) return hipErrorInvalidValue;
             const dim3 grid(static_cast<unsigned>(n_kt + units));
+            const int64_t n_first = few ? units : 0;
             const int whole = g.C % (16 / ES) == 0 ? 1 : 0;
 #define WG_KIT(VEC, RG)                                                                                           \
     hipLaunchKernelGGL((kernel_input_transform<Elem, TT, A, CO, VEC, RG, RELU>), grid, dim3(kInBlock), 0, stream, *ktab, \
-                       tab, wp, xs, up, vs, g, mp, kmp, n_kt, kt_rows, whole)
+                       tab, wp, xs, up, vs, g, mp, kmp, n_kt, n_first, kt_rows, whole)
             if constexpr (kPairs) {
                 if (pairs) WG_KIT(2, 1);
                 else WG_KIT(1, 1);

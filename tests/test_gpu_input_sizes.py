@@ -21,10 +21,14 @@ F8 = ("0,-1,1,-1/2,2,1/2,-2,a^2+1,inf", 8)
 
 
 @pytest.mark.parametrize("spec,m,dtype,shape", [
-    (WL.F4_A2P1, 4, "bf16", (1, 4, 128, 16)),     # 32 tiles x 8 pairs: one workgroup exactly
-    (WL.F4_A2P1, 4, "f16", (1, 4, 132, 16)),      # one tile more
-    (WL.F4_A2P1, 4, "bf16", (2, 13, 9, 15)),      # odd C: single channels, the last run past C
-    (WL.F4_A2P1, 4, "f16", (2, 13, 9, 18)),       # even C off the 16-byte chunk
+    (WL.F4_A2P1, 4, "bf16", (1, 4, 64, 16)),      # 16 tiles x 16 channels: one workgroup exactly
+    (WL.F4_A2P1, 4, "f16", (1, 4, 68, 16)),       # one tile more
+    (WL.F4_A2P1, 4, "bf16", (1, 128, 128, 64)),   # 256 workgroups of single channels
+    (WL.F4_A2P1, 4, "bf16", (1, 128, 129, 64)),   # a tile column more: pairs
+    (WL.F4_A2P1, 4, "f16", (1, 128, 132, 66)),    # pairs off the 16-byte chunk
+    (WL.F2_LINEAR, 2, "bf16", (2, 50, 94, 29)),   # many threads, odd C: single channels, units behind
+    (WL.F4_A2P1, 4, "bf16", (2, 13, 9, 15)),      # odd C: the last run past C
+    (WL.F4_A2P1, 4, "f16", (2, 13, 9, 18)),       # C off the 16-byte chunk
     (WL.F4_A2P1, 4, "bf16", (3, 5, 7, 1)),        # one channel of eight
     (WL.F6_TWO_QUAD, 6, "f32", (1, 96, 96, 128)),  # 2^15 threads: rows split over four workgroups
     (WL.F6_TWO_QUAD, 6, "f32", (1, 96, 97, 128)),  # just above: not split
