@@ -63,8 +63,6 @@ class VggStack:
         ws = torch.empty(need, dtype=torch.uint8, device=self.layers[0]["w"].device)
         for L in self.layers:
             L["plan"].bind_workspace(ws)
-            # the layer's plan can apply the ReLU before it to its own input
-            L["relu_in"] = L["plan"].relu_input_supported(N, L["hw"], L["hw"], L["C"], L["K"])
         self._shared_n = N
 
     def input(self, N, seed=0, device="cuda"):
@@ -84,7 +82,7 @@ class VggStack:
         self.share_workspace(x.shape[0])
         raw = False   # x is a conv output whose ReLU is still to be applied
         for L in self.layers:
-            if raw and not L["relu_in"]:
+            if raw and not L["plan"].relu_input_supported(*x.shape, L["K"]):
                 x, raw = relu_pool(x, False), False
             y = L["plan"].conv2d_relu_input(x, L["w"]) if raw else L["plan"].conv2d(x, L["w"])
             if keep:

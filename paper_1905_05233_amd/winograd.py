@@ -166,8 +166,9 @@ class Plan:
         return out.value
 
     def _need(self, sizes, query):
-        """Workspace bytes for a layer's sizes, asked of the library once per
-        plan and layer (they follow from the plan and the sizes alone)."""
+        """Workspace bytes (or the ReLU form's support) for a layer's sizes,
+        asked of the library once per plan and layer: they follow from the
+        plan and the sizes alone."""
         need = self._sizes.get(sizes)
         if need is None:
             need = query(*sizes)
@@ -234,9 +235,11 @@ class Plan:
 
     def relu_input_supported(self, N_, H, W, C, K):
         """Whether conv2d_relu_input takes this layer."""
-        out = ctypes.c_int()
-        N.check(self._lib.winograd_relu_input_supported(self._h, N_, H, W, C, K, ctypes.byref(out)))
-        return bool(out.value)
+        def query(_, *sizes):
+            out = ctypes.c_int()
+            N.check(self._lib.winograd_relu_input_supported(self._h, *sizes, ctypes.byref(out)))
+            return bool(out.value)
+        return self._need(("relu", N_, H, W, C, K), query)
 
     def conv2d_relu_input(self, x, w):
         """conv2d of ReLU(x): the same bits as conv2d(relu_pool(x, False), w)

@@ -66,3 +66,16 @@ def test_relu_input_refused():
         assert not p.relu_input_supported(1, 9, 9, 3, 40)
         with pytest.raises(WinogradError, match="UNSUPPORTED"):
             p.conv2d_relu_input(x, w)
+
+
+def test_stack_with_a_plan_exchanged_after_a_pass():
+    """A layer's plan replaced by one without the ReLU form: the ReLU kernel runs before it."""
+    from paper_1905_05233_amd.vgg import VggStack
+    from paper_1905_05233_amd.winograd import Plan
+    s = VggStack(dtype="bf16", plans=[WL.PlanSpec(WL.F4_A2P1, 4)] * 13)
+    x = s.input(1)
+    s.forward(x)
+    s.layers[1]["plan"] = Plan(WL.F4_A2P1, m=4, dtype="bf16", generic_transforms=True)
+    got = s.forward(x)
+    want, _ = s.forward(x, keep=True)
+    assert torch.equal(got, want)
