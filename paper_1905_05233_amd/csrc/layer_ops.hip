@@ -12,6 +12,7 @@
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
+#include <type_traits>
 
 #include "device_common.hpp"
 #include "kernels.hpp"
@@ -157,11 +158,13 @@ __global__ __launch_bounds__(kOpBlock) void direct_f64_kernel(const Elem* __rest
 //
 // What bounds it: the matrix cores (64 clocks per instruction), and for layers of
 // few blocks the latency of a chunk.  2x56x56, 128 -> 128 (1.85 GFLOP): 2650 us
-// with one thread per output, 74 us here (25 TFLOP/s; 196 blocks of four waves
-// leave 60 of the 256 CUs idle); 2x28x28, 512 -> 512: 13900 and 290 us.
+// with one thread per output, 64 us here (29 TFLOP/s; 196 blocks of four waves
+// leave 60 of the 256 CUs idle); 2x28x28, 512 -> 512: 13900 and 290 us
+// (the latter with 16-bit values still widened at the load).
 typedef double f64x4 __attribute__((ext_vector_type(4)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
+typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 constexpr int kF64Chunk = 32;
 constexpr int kF64Row = kF64Chunk + 4;   // floats per LDS row: 16-byte aligned, off the bank period
 
@@ -172,27 +175,39 @@ struct F64Geometry {
     uint32_t xbytes, wbytes;    // both below kOob
 };
 
-// four consecutive values of R, widened to fp32 (V4: one aligned load)
-template <typename Elem, bool V4>
-__device__ __forceinline__ f32x4 load_run4(__amdgpu_buffer_rsrc_t r, const uint32_t (&off)[4]) {
-    using S = Storage<Elem>;
-    f32x4 f;
-    if constexpr (V4 && sizeof(Elem) == 4) {
-        f = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(r, off[0], 0, 0));
-    } else if constexpr (V4) {
-        const u32x2 v = __builtin_amdgcn_raw_buffer_load_b64(r, off[0], 0, 0);
+// Four consecutive values of R as loaded (V4: one aligned load), and widened to
+// fp32.  The two are apart so that the wait for a load comes where the values
+// are parked, behind the products: widened at the load, 16-bit layers waited
+// ahead of every chunk's products (2x56x56, 128 -> 128 in bf16 72.7 us, now 63.8).
+template <typename Elem, bool V4> struct Run4 {
+    using Bits = std::conditional_t<V4 && sizeof(Elem) == 2, u32x2, u32x4>;
+    static __device__ __forceinline__ Bits load(__amdgpu_buffer_rsrc_t r, const uint32_t (&off)[4]) {
+        if constexpr (V4 && sizeof(Elem) == 4) {
+            return __builtin_amdgcn_raw_buffer_load_b128(r, off[0], 0, 0);
+        } else if constexpr (V4) {
+            return __builtin_amdgcn_raw_buffer_load_b64(r, off[0], 0, 0);
+        } else {
+            Bits b;
 #pragma unroll
-        for (int e = 0; e < 4; ++e)
-            f[e] = S::to_f32(__builtin_bit_cast(Elem, static_cast<uint16_t>(v[e >> 1] >> (16 * (e & 1)))));
-    } else {
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            if constexpr (sizeof(Elem) == 4) f[e] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(r, off[e], 0, 0));
-            else f[e] = S::to_f32(__builtin_bit_cast(Elem, static_cast<uint16_t>(__builtin_amdgcn_raw_buffer_load_b16(r, off[e], 0, 0))));
+            for (int e = 0; e < 4; ++e) {
+                if constexpr (sizeof(Elem) == 4) b[e] = __builtin_amdgcn_raw_buffer_load_b32(r, off[e], 0, 0);
+                else b[e] = static_cast<uint16_t>(__builtin_amdgcn_raw_buffer_load_b16(r, off[e], 0, 0));
+            }
+            return b;
         }
     }
-    return f;
-}
+    static __device__ __forceinline__ f32x4 widen(const Bits& b) {
+        using S = Storage<Elem>;
+        f32x4 f;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            if constexpr (sizeof(Elem) == 4) f[e] = __uint_as_float(b[e]);
+            else if constexpr (V4) f[e] = S::to_f32(__builtin_bit_cast(Elem, static_cast<uint16_t>(b[e >> 1] >> (16 * (e & 1)))));
+            else f[e] = S::to_f32(__builtin_bit_cast(Elem, static_cast<uint16_t>(b[e])));
+        }
+        return f;
+    }
+};
 
 template <typename Elem, int KH, int BM, int BN, int WT, bool V4>
 __global__ __launch_bounds__(256) void direct_f64_mfma_kernel(const Elem* __restrict__ x, const Elem* __restrict__ w,
@@ -229,7 +244,8 @@ __global__ __launch_bounds__(256) void direct_f64_mfma_kernel(const Elem* __rest
         const int64_t k = n0 + row0 + 32 * i;
         woff[i] = k < g.K ? static_cast<uint32_t>(k * g.R * ES) : kOob;
     }
-    f32x4 xr[kXI], wr[kWI];
+    using Run = Run4<Elem, V4>;
+    typename Run::Bits xr[kXI], wr[kWI];
     bool odd = false;   // an infinite or NaN weight
     auto load = [&](int r0) __attribute__((always_inline)) {
         int di[4], dj[4];
@@ -249,28 +265,31 @@ __global__ __launch_bounds__(256) void direct_f64_mfma_kernel(const Elem* __rest
             uint32_t off[4];
 #pragma unroll
             for (int e = 0; e < (V4 ? 1 : 4); ++e) {
-                const int h = xh[i] + di[e], v = xw[i] + dj[e];
-                off[e] = in[e] && h >= 0 && h < g.H && v >= 0 && v < g.W ? xoff[i] + dx[e] : kOob;
+                const uint32_t h = static_cast<uint32_t>(xh[i] + di[e]), v = static_cast<uint32_t>(xw[i] + dj[e]);
+                // & and not &&: a select, no branch between the loads
+                const bool ok = in[e] & (h < static_cast<uint32_t>(g.H)) & (v < static_cast<uint32_t>(g.W));
+                off[e] = ok ? xoff[i] + dx[e] : kOob;
             }
-            xr[i] = load_run4<Elem, V4>(rx, off);
+            xr[i] = Run::load(rx, off);
         }
 #pragma unroll
         for (int i = 0; i < kWI; ++i) {
             uint32_t off[4];
 #pragma unroll
             for (int e = 0; e < (V4 ? 1 : 4); ++e)
-                off[e] = in[e] && woff[i] != kOob ? woff[i] + static_cast<uint32_t>((r0 + q4 + e) * ES) : kOob;
-            wr[i] = load_run4<Elem, V4>(rw, off);
+                off[e] = in[e] & (woff[i] != kOob) ? woff[i] + static_cast<uint32_t>((r0 + q4 + e) * ES) : kOob;
+            wr[i] = Run::load(rw, off);
         }
     };
     auto park = [&](int buf) __attribute__((always_inline)) {
 #pragma unroll
-        for (int i = 0; i < kXI; ++i) *reinterpret_cast<f32x4*>(&st[buf][(row0 + 32 * i) * kF64Row + q4]) = xr[i];
+        for (int i = 0; i < kXI; ++i) *reinterpret_cast<f32x4*>(&st[buf][(row0 + 32 * i) * kF64Row + q4]) = Run::widen(xr[i]);
 #pragma unroll
         for (int i = 0; i < kWI; ++i) {
-            *reinterpret_cast<f32x4*>(&st[buf][(BM + row0 + 32 * i) * kF64Row + q4]) = wr[i];
+            const f32x4 f = Run::widen(wr[i]);
+            *reinterpret_cast<f32x4*>(&st[buf][(BM + row0 + 32 * i) * kF64Row + q4]) = f;
 #pragma unroll
-            for (int e = 0; e < 4; ++e) odd |= !(__builtin_fabsf(wr[i][e]) < __builtin_inff());
+            for (int e = 0; e < 4; ++e) odd |= !(__builtin_fabsf(f[e]) < __builtin_inff());
         }
     };
     f64x4 acc[WT][WT];
