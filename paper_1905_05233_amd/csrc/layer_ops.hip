@@ -215,6 +215,7 @@ __global__ __launch_bounds__(256) void direct_f64_mfma_kernel(const Elem* __rest
     constexpr int ES = static_cast<int>(sizeof(Elem));
     constexpr int kWN = BN / (16 * WT);        // waves along the output channels
     static_assert((BM / (16 * WT)) * kWN == 4, "four waves");
+    static_assert(WT == 1 || WT == 2, "the wait behind the products names its sums");
     constexpr int kXI = BM / 32, kWI = BN / 32;   // row groups of 32 that a thread loads for
     __shared__ __attribute__((aligned(16))) float st[2][(BM + BN) * kF64Row];
     const int tid = threadIdx.x;
@@ -324,14 +325,18 @@ __global__ __launch_bounds__(256) void direct_f64_mfma_kernel(const Elem* __rest
                             static_cast<double>(a[i][e]), static_cast<double>(b[j][e]),
                             s == 0 && e == 0 ? f64x4{0.0, 0.0, 0.0, 0.0} : part[i][j], 0, 0, 0);
         }
-        // Wait out the last product before its result is read.  (With the
-        // accumulators carried across the loop the compiler read the last one's
-        // top register right behind a branch, ahead of its own wait states: an
-        // accvgpr_read of the eighth register before the s_nop in the assembly,
-        // wrong rows 12 .. 15 of a tile on the GPU.)
-        __builtin_amdgcn_sched_barrier(0);
-        asm volatile("s_nop 15\n\ts_nop 15" ::: "memory");
-        __builtin_amdgcn_sched_barrier(0);
+        // Wait out the last product before its result is read (the compiler
+        // keeps 19 wait states between the two on gfx950).  Without this wait
+        // it was seen to place a copy of a result's last register ahead of its
+        // own wait states, where the block ends in a branch (an accvgpr_read two
+        // states behind the product; rows 12 .. 15 of a tile came out wrong).
+        // The sums are operands of the wait, in the registers that the products
+        // write, so what reads them comes behind it;
+        // tests/test_f64_waits.py checks the code of every instance.
+        if constexpr (WT == 1)
+            asm volatile("s_nop 15\n\ts_nop 2" : "+a"(part[0][0]));
+        else
+            asm volatile("s_nop 15\n\ts_nop 2" : "+a"(part[0][0]), "+a"(part[0][1]), "+a"(part[1][0]), "+a"(part[1][1]));
         // a chunk's sum, then the chunks': fewer roundings than one chain over R
 #pragma unroll
         for (int i = 0; i < WT; ++i)
