@@ -19,14 +19,13 @@
 #include "coefs.hpp"
 #include "device_common.hpp"
 #include "kernels.hpp"
+#include "launch_split.hpp"
 
 namespace wg {
 
-constexpr int kOutBlock = 256;
-
 struct OutputMap {
     FastDiv per_tile, tw, th;   // divisors: threads per tile, tiles per row, tile rows
-    int64_t threads;            // (tile, channel) pairs of this launch (below 2^31)
+    int64_t threads;            // (tile, channel) pairs of this launch (at most kOutMaxPairs)
     int64_t tile0;              // its first tile
 };
 
@@ -66,8 +65,6 @@ __device__ __forceinline__ void output_regs_rows(const OutputTable& tab, const f
         }
     }
 }
-
-constexpr int kOutGroups = 2;   // row groups
 
 template <typename Elem, int MM, int ALPHA, class CO>
 __global__ __launch_bounds__(kOutBlock) void output_transform_regs(OutputTable tab, const float* __restrict__ Mx,

@@ -480,19 +480,18 @@ hipError_t launch_in(const Geometry& g, const KernelTable* ktab, const InputTabl
 
 template <typename Elem, int TT, int A, class CO>
 hipError_t launch_ot(const Geometry& g, const OutputTable& tab, const float* M, Elem* yp, hipStream_t stream) {
-    if (g.T * g.K >= kOutManyThreads && g.T < (int64_t(1) << 31) && g.K < (int64_t(1) << 31)) {
-        // launches of whole tiles whose thread ids fit 31 bits (one but for huge layers)
+    if (g.T * g.K >= kOutManyThreads && g.T < (int64_t(1) << 31) && g.K <= kOutMaxPairs) {
+        // launches of whole tiles (one but for huge layers)
         OutputMap mp;
         mp.per_tile = make_fastdiv(g.K);
         mp.tw = make_fastdiv(g.tw);
         mp.th = make_fastdiv(g.th);
-        const int64_t per = std::max<int64_t>(1, 0x7fffffff / g.K);
+        const int64_t per = output_tiles_per_launch(g.K);
         for (int64_t t0 = 0; t0 < g.T; t0 += per) {
             mp.tile0 = t0;
             mp.threads = std::min<int64_t>(per, g.T - t0) * g.K;
-            const int64_t blocks = (mp.threads + kOutBlock - 1) / kOutBlock * kOutGroups;
-            hipLaunchKernelGGL((output_transform_regs<Elem, TT - 2, A, CO>), dim3(static_cast<unsigned>(blocks)),
-                               dim3(kOutBlock), 0, stream, tab, M, yp, g, mp);
+            hipLaunchKernelGGL((output_transform_regs<Elem, TT - 2, A, CO>),
+                               dim3(static_cast<unsigned>(output_blocks(mp.threads))), dim3(kOutBlock), 0, stream, tab, M, yp, g, mp);
             const hipError_t e = hipGetLastError();
             if (e != hipSuccess) return e;
         }

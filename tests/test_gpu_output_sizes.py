@@ -35,3 +35,22 @@ def test_output_transform_forms_agree(spec, m, shape, dtype):
     for n in range(N):
         one = p.output_transform(M[:, n * per:(n + 1) * per].contiguous(), 1, H, W, K)
         assert torch.equal(y[n:n + 1], one), n
+
+
+def test_output_transform_over_one_launch():
+    """33 images of 2^26 (tile, channel) pairs: the first launch ends inside the 32nd."""
+    from paper_1905_05233_amd.winograd import Plan
+    N, H, W, K = 33, 2048, 2048, 64
+    p = Plan(WL.F2_LINEAR, m=2, dtype="f16")
+    g = p.geometry(N, H, W, 8, K)
+    per = g["T"] // N
+    assert g["T"] * K > 1 << 31
+    if torch.cuda.mem_get_info()[0] < 200 << 30:
+        pytest.skip("needs 200 GiB of device memory")
+    M = torch.empty((p.alpha ** 2, g["T"], g["Kp"]), device="cuda").uniform_(-1.0, 1.0)
+    y = p.output_transform(M, N, H, W, K)
+    for n in (0, 31, 32):
+        one = p.output_transform(M[:, n * per:(n + 1) * per].contiguous(), 1, H, W, K)
+        assert torch.equal(y[n:n + 1], one), n
+    del M, y, one
+    torch.cuda.empty_cache()
