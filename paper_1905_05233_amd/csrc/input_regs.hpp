@@ -25,18 +25,17 @@
 #include "coefs.hpp"
 #include "device_common.hpp"
 #include "kernels.hpp"
+#include "launch_split.hpp"
 
 namespace wg {
 
-constexpr int kInBlock = 256;
-constexpr int64_t kInMaxBytes = int64_t(1) << 30;   // x of one launch: below the out-of-range offsets used here
-
-// What a launch of the register form covers: whole images whose x is at most
-// kInMaxBytes.
+// What a launch of the register form covers: whole images, or a band of tile
+// rows of one image (launch_split.hpp).
 struct InputMap {
-    FastDiv per_tile, tw, th;   // divisors: threads per tile, tiles per row, tile rows
+    FastDiv per_tile, tw, th;   // divisors: threads per tile, tiles per row, tile rows of an image or the band
     int64_t threads;            // (tile, run) pairs of this launch
-    uint32_t xbytes;            // bytes of its images (at most kInMaxBytes)
+    uint32_t xbytes;            // bytes of its pixels (at most kInMaxBytes)
+    int h, up;                  // rows of pixels of an image or the band; the first window row is row -up of them
     int64_t plane;              // bytes of a plane of V (all images)
 };
 
@@ -153,7 +152,7 @@ __device__ __forceinline__ void input_regs_groups(const InputTable& tab, const t
 // The window (columns first: a column's loads are issued together) and the
 // thread's place in V.
 //
-// Images of at most kInMaxBytes: 32-bit offsets through a buffer descriptor; a
+// 32-bit offsets through a buffer descriptor (at most kInMaxBytes of pixels); a
 // row or column outside the image gets an offset past every record, so its
 // loads return zero without a branch (valid sums stay below 2^30).
 template <typename Elem, int TT, int VEC>
@@ -167,13 +166,13 @@ __device__ __forceinline__ void input_window(const Elem* __restrict__ x, const G
     const int tx = static_cast<int>(tile - row * mp.tw.d);
     const uint32_t n = fast_div(row, mp.th);
     const int ty = static_cast<int>(row - n * mp.th.d);
-    const int H = static_cast<int>(geo.H), W = static_cast<int>(geo.W), C = static_cast<int>(geo.C);
+    const int H = mp.h, W = static_cast<int>(geo.W), C = static_cast<int>(geo.C);
     const auto rx = __builtin_amdgcn_make_buffer_rsrc(const_cast<Elem*>(x), static_cast<short>(0),
                                                       static_cast<int>(mp.xbytes), static_cast<int>(kRsrcWord3));
     uint32_t ro[TT], co[TT];
 #pragma unroll
     for (int u = 0; u < TT; ++u) {
-        const int hr = ty * m - 1 + u;
+        const int hr = ty * m - mp.up + u;
         ro[u] = hr >= 0 && hr < H ? (n * static_cast<uint32_t>(H) + static_cast<uint32_t>(hr)) *
                                         static_cast<uint32_t>(W * C * ES)
                                   : 0x80000000u;
@@ -189,11 +188,14 @@ __device__ __forceinline__ void input_window(const Elem* __restrict__ x, const G
         for (int u = 0; u < TT; ++u) d[v][u] = InRun<Elem, VEC>::load(rx, ro[u] + co[v]);
 }
 
-// Larger images: 64-bit addresses, one channel per thread, loads behind their bounds.
-template <typename Elem, int TT>
+// Images of which one tile row's pixels exceed kInMaxBytes: 64-bit addresses,
+// loads behind their bounds.
+template <typename Elem, int TT, int VEC>
 __device__ __forceinline__ void input_window_big(const Elem* __restrict__ x, const Geometry& geo, int64_t gid,
-                                                 typename InRun<Elem, 1>::Bits (&d)[TT][TT]) {
-    const int64_t tile = gid / geo.Cp, c = gid % geo.Cp;
+                                                 typename InRun<Elem, VEC>::Bits (&d)[TT][TT]) {
+    using Bits = typename InRun<Elem, VEC>::Bits;
+    const int64_t runs = geo.Cp / VEC;
+    const int64_t tile = gid / runs, c = (gid - tile * runs) * VEC;
     const int64_t tx = tile % geo.tw, ty = (tile / geo.tw) % geo.th, n = tile / (geo.tw * geo.th);
 #pragma unroll
     for (int v = 0; v < TT; ++v)
@@ -202,8 +204,7 @@ __device__ __forceinline__ void input_window_big(const Elem* __restrict__ x, con
             const int64_t hr = ty * (TT - 2) - 1 + u, wc = tx * (TT - 2) - 1 + v;
             const bool in = hr >= 0 && hr < geo.H && wc >= 0 && wc < geo.W && c < geo.C;
             const Elem* src = x + ((n * geo.H + hr) * geo.W + wc) * geo.C + c;
-            d[v][u] = in ? *reinterpret_cast<const typename InRun<Elem, 1>::Bits*>(src)
-                         : typename InRun<Elem, 1>::Bits(0);
+            d[v][u] = in ? *reinterpret_cast<const Bits*>(src) : Bits(0);
         }
 }
 
@@ -224,7 +225,7 @@ __device__ __forceinline__ void input_regs_unit(const InputTable& tab, const Ele
     const int64_t gid = base + threadIdx.x;
     if (gid >= mp.threads) return;
     Bits d[TT][TT];
-    if constexpr (BIG) input_window_big<Elem, TT>(x, geo, gid, d);
+    if constexpr (BIG) input_window_big<Elem, TT, VEC>(x, geo, gid, d);
     else input_window<Elem, TT, VEC>(x, geo, mp, static_cast<uint32_t>(gid), d);
     unsigned char* out = V + base * (VEC * ES);
     const uint32_t lo = threadIdx.x * (VEC * ES);

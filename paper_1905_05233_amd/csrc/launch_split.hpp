@@ -24,4 +24,31 @@ constexpr int64_t kOutMaxPairs =
 constexpr int64_t output_tiles_per_launch(int64_t K) { return kOutMaxPairs / K; }
 constexpr int64_t output_blocks(int64_t pairs) { return (pairs + kOutBlock - 1) / kOutBlock * kOutGroups; }
 
+// Input transform in registers: 32-bit offsets into the pixels that a launch
+// reads, at most kInMaxBytes of them (below the out-of-range offsets that its
+// kernel uses), and thread ids below 2^31.
+constexpr int kInBlock = 256;
+constexpr int64_t kInMaxBytes = int64_t(1) << 30;
+// What one launch covers: `images` whole images, or, where one image is too
+// large, `rows` tile rows of one.  rows = 0: not even one tile row fits.
+struct InputSplit {
+    int64_t images, rows;
+};
+// row_bytes: of a row of pixels; tile_row_threads: threads of a row of tiles.
+constexpr InputSplit input_split(int64_t H, int64_t row_bytes, int64_t tile_rows, int64_t tile_row_threads, int m) {
+    const int64_t img_bytes = H * row_bytes, img_threads = tile_rows * tile_row_threads;
+    if (img_bytes <= kInMaxBytes && img_threads <= 0x7fffffff)
+        return {std::min<int64_t>(kInMaxBytes / img_bytes, 0x7fffffff / img_threads), tile_rows};
+    // r tile rows read at most r m + 2 rows of pixels
+    const int64_t rows = std::min<int64_t>((kInMaxBytes / row_bytes - 2) / m, 0x7fffffff / tile_row_threads);
+    return {1, std::max<int64_t>(0, std::min(rows, tile_rows))};
+}
+// The rows of pixels that tile rows r0 .. r0 + rows - 1 read: [first, end).
+struct InputBand {
+    int64_t first, end;
+};
+constexpr InputBand input_band(int64_t H, int64_t r0, int64_t rows, int m) {
+    return {std::max<int64_t>(0, r0 * m - 1), std::min<int64_t>(H, (r0 + rows) * m + 1)};
+}
+
 }  // namespace wg

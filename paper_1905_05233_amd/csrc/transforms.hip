@@ -386,51 +386,75 @@ hipError_t launch_kernel_transform_t(const Geometry& g, const KernelTable& tab, 
 }
 
 // One launch of each kernel shape, with the coefficient source CO.  The images
-// go in groups whose bytes and threads fit 32-bit arithmetic (one group but for
-// inputs over 1 GiB); with ktab the first group's launch carries the kernel
-// transform.  RELU: of ReLU(x) (images within one launch's reach).
+// go in groups, and an image over 1 GiB in bands of tile rows, whose bytes and
+// threads fit 32-bit arithmetic; with ktab the first launch carries the kernel
+// transform.  RELU: of ReLU(x) (images of at most kInMaxBytes).
+//
+// Bands, and not one launch with 64-bit addresses: 1x8192x8192x64 in bf16 with
+// alpha' = 7 (8.6 GB of x) 16.3 ms so with one channel per thread, 7.1 ms in
+// bands of pairs.  Only images whose tile rows are too large for a band each
+// are left to 64-bit addresses.
 template <typename Elem, int TT, int A, class CO, bool RELU = false>
 hipError_t launch_in(const Geometry& g, const KernelTable* ktab, const InputTable& tab, const Elem* wp, const Elem* xp,
                      Elem* up, Elem* vp, hipStream_t stream) {
     constexpr int ES = static_cast<int>(sizeof(Elem));
+    constexpr int kM = TT - 2;
     constexpr bool kPairs = input_pairs<Elem>(TT);
     constexpr int kRG = input_groups(TT);
     const bool few = g.T * g.Cp <= kInFirstUnits * kInBlock;
     const bool pairs = kPairs && g.C % 2 == 0 && !few;
     const int vec = pairs ? 2 : 1;
-    const int64_t tiles_img = g.th * g.tw, thr_img = tiles_img * (g.Cp / vec), x_img = g.H * g.W * g.C;
+    const int64_t tiles_img = g.th * g.tw, thr_row = g.tw * (g.Cp / vec), row = g.W * g.C, x_img = g.H * row;
     InputMap mp;
     mp.per_tile = make_fastdiv(g.Cp / vec);
     mp.tw = make_fastdiv(g.tw);
-    mp.th = make_fastdiv(g.th);
     mp.plane = g.T * g.Cp * ES;
-    const bool big = x_img * ES > kInMaxBytes || thr_img > 0x7fffffff;
-    if (big && RELU) return hipErrorInvalidValue;
-    if (big) {
-        // larger images: the kernel transform apart, 64-bit addresses
-        mp.threads = g.T * g.Cp;
-        mp.xbytes = 0;
-        const int64_t blocks = (mp.threads + kInBlock - 1) / kInBlock;
-        if (blocks > 0x7fffffff) return hipErrorInvalidValue;
-        if (ktab) {
-            constexpr int D = sizeof(Elem) == 4 ? 0 : __is_same(Elem, bf16_t) ? 2 : 1;
-            const hipError_t e = launch_kernel_transform_t<D>(g, *ktab, wp, up, stream);
-            if (e != hipSuccess) return e;
+    const InputSplit sp = input_split(g.H, row * ES, g.th, thr_row, kM);
+    if (sp.rows == 0) {
+        // rows of over kInMaxBytes / t: the kernel transform apart, 64-bit addresses
+        if constexpr (RELU) {
+            return hipErrorInvalidValue;
+        } else {
+            mp.th = make_fastdiv(g.th);
+            mp.threads = g.T * (g.Cp / vec);
+            mp.xbytes = 0;
+            mp.h = mp.up = 0;
+            const int64_t blocks = (mp.threads + kInBlock - 1) / kInBlock;
+            if (blocks * kInBlock > kMaxWorkItems) return hipErrorInvalidValue;
+            if (ktab) {
+                constexpr int D = sizeof(Elem) == 4 ? 0 : __is_same(Elem, bf16_t) ? 2 : 1;
+                const hipError_t e = launch_kernel_transform_t<D>(g, *ktab, wp, up, stream);
+                if (e != hipSuccess) return e;
+            }
+#define WG_IT_BIG(VEC)                                                                                             \
+    hipLaunchKernelGGL((input_transform<Elem, TT, A, CO, VEC, 1, true, false>), dim3(static_cast<unsigned>(blocks)), \
+                       dim3(kInBlock), 0, stream, tab, xp, reinterpret_cast<unsigned char*>(vp), g, mp)
+            if constexpr (kPairs) {
+                if (pairs) WG_IT_BIG(2);
+                else WG_IT_BIG(1);
+            } else {
+                WG_IT_BIG(1);
+            }
+#undef WG_IT_BIG
+            return hipGetLastError();
         }
-        hipLaunchKernelGGL((input_transform<Elem, TT, A, RuntimeCoefs, 1, 1, true, false>), dim3(static_cast<unsigned>(blocks)),
-                           dim3(kInBlock), 0, stream, tab, xp, reinterpret_cast<unsigned char*>(vp), g, mp);
-        return hipGetLastError();
     }
-    const int64_t per = std::max<int64_t>(1, std::min<int64_t>(kInMaxBytes / (x_img * ES), 0x7fffffff / thr_img));
-    for (int64_t n0 = 0; n0 < g.N; n0 += per) {
-        const int64_t nn = std::min<int64_t>(per, g.N - n0);
-        mp.threads = nn * thr_img;
-        mp.xbytes = static_cast<uint32_t>(nn * x_img * ES);
-        const Elem* xs = xp + n0 * x_img;
-        auto* vs = reinterpret_cast<unsigned char*>(vp) + n0 * tiles_img * g.Cp * ES;
+    // whole images (one band each, every row of it) or bands of one image
+    const bool whole_images = sp.rows == g.th;
+    for (int64_t n0 = 0, r0 = 0; n0 < g.N;) {
+        const int64_t nn = std::min<int64_t>(sp.images, g.N - n0), nr = std::min<int64_t>(sp.rows, g.th - r0);
+        const InputBand band = whole_images ? InputBand{0, g.H} : input_band(g.H, r0, nr, kM);
+        const bool first = n0 == 0 && r0 == 0;
+        mp.th = make_fastdiv(nr);
+        mp.threads = nn * nr * thr_row;
+        mp.h = static_cast<int>(band.end - band.first);
+        mp.up = static_cast<int>(band.first - r0 * kM + 1);   // 1 at the top of an image, else 0
+        mp.xbytes = static_cast<uint32_t>(nn * mp.h * row * ES);
+        const Elem* xs = xp + n0 * x_img + band.first * row;
+        auto* vs = reinterpret_cast<unsigned char*>(vp) + (n0 * tiles_img + r0 * g.tw) * g.Cp * ES;
         const bool split = kRG > 1 && mp.threads <= kInFewThreads;
         const int64_t units = (mp.threads + kInBlock - 1) / kInBlock * (split ? kRG : 1);
-        if (ktab && n0 == 0) {
+        if (ktab && first) {
             // the kernel transform's workgroups, a multiple of 8, so the input
             // transform's ids keep their XCD (id mod 8).  One thread for every
             // row a of a (k, 4-channel run) loads the taps once, but needs
@@ -474,6 +498,11 @@ hipError_t launch_in(const Geometry& g, const KernelTable* ktab, const InputTabl
         }
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
+        r0 += nr;
+        if (r0 == g.th) {
+            r0 = 0;
+            n0 += nn;
+        }
     }
     return hipSuccess;
 }

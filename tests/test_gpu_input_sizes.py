@@ -1,7 +1,7 @@
 """The input transform where its launch changes form: pairs of channels or
 single ones, domain rows split over workgroups, the last workgroup partly
-filled, batches whose input exceeds the 1 GiB that one launch addresses, and
-single images beyond it.  V is compared bit for bit: with the oracle's at small
+filled, batches whose input exceeds the 1 GiB that one launch addresses, single
+images beyond it and single rows.  V is compared bit for bit: with the oracle's at small
 sizes, and at large ones with the V of a crop or of single images, whose tiles
 see the same pixels.
 """
@@ -70,17 +70,65 @@ def test_input_transform_batch_over_one_launch(dtype, C):
         assert torch.equal(V[:, n * per:(n + 1) * per], one), n
 
 
-@pytest.mark.parametrize("dtype,C", [("f32", 8), ("bf16", 15)])
-def test_input_transform_image_over_one_launch(dtype, C):
-    """One image over 1 GiB: its first and last tile rows against a crop's."""
+def _bits(t):
+    return t.view(torch.int32 if t.element_size() == 4 else torch.int16)
+
+
+def _special(x, seed):
+    """A few infinities and NaN spread over x, some beside its edges."""
+    flat = x.view(-1)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(seed)
+    at = torch.randint(0, flat.numel(), (4096,), generator=g, device="cuda")
+    flat[at[:2048]] = float("inf")
+    flat[at[2048:3072]] = float("-inf")
+    flat[at[3072:]] = float("nan")
+    x[:, 0, 0], x[:, -1, -1] = float("inf"), float("nan")
+
+
+@pytest.mark.parametrize("spec,m,dtype,H,C", [
+    (WL.F2_LINEAR, 2, "f32", 4100, 8),
+    (WL.F2_LINEAR, 2, "bf16", 8900, 15),
+    (WL.F4_A2P1, 4, "f16", 5003, 16),     # built-in coefficients, pairs, a partial last tile row
+    (WL.F6_TWO_QUAD, 6, "bf16", 4999, 16),
+], ids=str)
+def test_input_transform_image_over_one_launch(spec, m, dtype, H, C):
+    """One image over 1 GiB, infinities and NaN in it, against
+    crops of it: all of V, the tiles at a crop's cut edges apart."""
+    from paper_1905_05233_amd.winograd import Plan
+    p = Plan(spec, m=m, dtype=dtype)
+    W = 8192
+    x = _random((1, H, W, C), dtype, 2)
+    _special(x, 3)
+    assert x.numel() * x.element_size() > 1 << 30
+    w = _random((5, 3, 3, C), dtype, 4)
+    U, V = p.kernel_input_transform(w, x)
+    assert torch.equal(U, p.kernel_transform(w))
+    assert torch.equal(_bits(p.input_transform(x)), _bits(V))
+    th, tw, step = -(-H // m), -(-W // m), 600
+    for r in range(0, th, step):
+        r0, r1 = max(0, r - 1), min(th, r + step + 1)   # a tile row more on each side
+        crop = p.input_transform(x[:, r0 * m:min(H, r1 * m)].contiguous())
+        a, b = (r - r0) * tw, (min(th, r + step) - r0) * tw
+        assert torch.equal(_bits(V[:, r * tw:r * tw + b - a]), _bits(crop[:, a:b])), r
+
+
+@pytest.mark.parametrize("dtype,C", [("bf16", 16), ("f16", 15), ("f32", 8)])
+def test_input_transform_row_over_one_launch(dtype, C):
+    """Rows of pixels of which four exceed 1 GiB: 64-bit addresses."""
     from paper_1905_05233_amd.winograd import Plan
     p = Plan(WL.F2_LINEAR, m=2, dtype=dtype)
-    H, W = 4100 + (4800 if dtype == "bf16" else 0), 8192
-    x = _random((1, H, W, C), dtype, 2)
-    assert x.numel() * x.element_size() > 1 << 30
-    V = p.input_transform(x)
-    tw = W // 2
-    top = p.input_transform(x[:, :42].contiguous())           # tile rows 0 .. 19 see rows below 41
-    assert torch.equal(V[:, :20 * tw], top[:, :20 * tw])
-    end = p.input_transform(x[:, H - 42:].contiguous())       # the last 20 tile rows
-    assert torch.equal(V[:, -20 * tw:], end[:, -20 * tw:])
+    W, m, n = 1 << 24, 2, 1 << 12
+    x = _random((1, 3, W, C), dtype, 5)
+    _special(x, 6)
+    assert 4 * W * C * x.element_size() > 1 << 30
+    w = _random((5, 3, 3, C), dtype, 7)
+    U, V = p.kernel_input_transform(w, x)
+    assert torch.equal(U, p.kernel_transform(w))
+    tw = W // m
+    for c0 in (0, W // 2, W - n):           # crops of n columns, their cut edges apart
+        crop = p.input_transform(x[:, :, c0:c0 + n].contiguous())
+        for ty in range(2):
+            a, b = (0 if c0 == 0 else 1), n // m - (0 if c0 == W - n else 1)
+            got = V[:, ty * tw + c0 // m + a:ty * tw + c0 // m + b]
+            assert torch.equal(_bits(got), _bits(crop[:, ty * (n // m) + a:ty * (n // m) + b])), (c0, ty)
