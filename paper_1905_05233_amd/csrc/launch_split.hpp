@@ -1,4 +1,5 @@
-// How layers too large for one launch are split (host arithmetic only).
+// How layers too large for one launch are split, and which form of the float64
+// convolution a layer takes (host arithmetic only).
 //
 // HIP takes launches of fewer than 2^32 work-items along x (gridDim.x *
 // blockDim.x), whatever the ids that the kernel itself computes.
@@ -49,6 +50,22 @@ struct InputBand {
 };
 constexpr InputBand input_band(int64_t H, int64_t r0, int64_t rows, int m) {
     return {std::max<int64_t>(0, r0 * m - 1), std::min<int64_t>(H, (r0 + rows) * m + 1)};
+}
+
+// Float64 direct convolution: one thread per output, or the matrix cores with
+// 32 x 32, 64 x 64 or 128 x 32 (pixels x output channels) outputs per workgroup.
+enum F64Form { kF64PerOutput, kF64Block32, kF64Block64, kF64Block128x32 };
+// taps: 9 or 3; es: bytes of a value.  The matrix cores where a block's columns
+// and chunk are mostly filled and 32-bit offsets reach both inputs; small layers
+// in 32 x 32 outputs, for more workgroups.
+constexpr F64Form f64_form(int64_t pixels, int64_t C, int64_t K, int taps, int64_t es, int cus) {
+    const int64_t R = taps * C;
+    if (!(K > 8 && R > 16 && R < (int64_t(1) << 30) && pixels * C * es < 0xfffffff0LL && K * R * es < 0xfffffff0LL &&
+          pixels / 32 < 0x7fffffff && K / 32 < 0xffff))
+        return kF64PerOutput;
+    const int64_t bn = K > 32 ? 64 : 32, bm = 4096 / bn;
+    if (((pixels + bm - 1) / bm) * ((K + bn - 1) / bn) < cus / 2) return kF64Block32;
+    return bn == 64 ? kF64Block64 : kF64Block128x32;
 }
 
 }  // namespace wg

@@ -16,6 +16,7 @@
 
 #include "device_common.hpp"
 #include "kernels.hpp"
+#include "launch_split.hpp"
 
 namespace wg {
 
@@ -159,12 +160,10 @@ __global__ __launch_bounds__(kOpBlock) void direct_f64_kernel(const Elem* __rest
 // What bounds it: the matrix cores (64 clocks per instruction), and for layers of
 // few blocks the latency of a chunk.  2x56x56, 128 -> 128 (1.85 GFLOP): 2650 us
 // with one thread per output, 64 us here (29 TFLOP/s; 196 blocks of four waves
-// leave 60 of the 256 CUs idle); 2x28x28, 512 -> 512: 13900 and 290 us
-// (the latter with 16-bit values still widened at the load).
+// leave 60 of the 256 CUs idle); 2x28x28, 512 -> 512: 13900 and 242 us.
 typedef double f64x4 __attribute__((ext_vector_type(4)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
-typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 constexpr int kF64Chunk = 32;
 constexpr int kF64Row = kF64Chunk + 4;   // floats per LDS row: 16-byte aligned, off the bank period
 
@@ -467,17 +466,12 @@ hipError_t launch_direct_f64_t(const void* x, const void* w, double* y, int64_t 
     const auto* xp = static_cast<const Elem*>(x);
     const auto* wp = static_cast<const Elem*>(w);
     const int64_t R = static_cast<int64_t>(kh) * 3 * C, pixels = N * H * W, es = sizeof(Elem);
-    // the matrix cores where a block's columns and chunk are mostly filled and
-    // 32-bit offsets reach both inputs
-    if (K > 8 && R > 16 && R < (int64_t(1) << 30) && pixels * C * es < 0xfffffff0LL && K * R * es < 0xfffffff0LL &&
-        pixels / 32 < 0x7fffffff && K / 32 < 0xffff) {
+    const F64Form form = f64_form(pixels, C, K, kh * 3, es, device_cu_count());
+    if (form != kF64PerOutput) {
         const F64Geometry g{H, W, C, K, pixels, static_cast<int>(R), make_fastdiv(C),
                             static_cast<uint32_t>(pixels * C * es), static_cast<uint32_t>(K * R * es)};
-        // small layers: 32 x 32 outputs per workgroup, for more of them
-        const int64_t bn = K > 32 ? 64 : 32, bm = 4096 / bn;
-        const bool small = ((pixels + bm - 1) / bm) * ((K + bn - 1) / bn) < device_cu_count() / 2;
-        if (small) return launch_f64_mfma<Elem, 32, 32, 1>(g, xp, wp, y, kh, stream);
-        if (bn == 64) return launch_f64_mfma<Elem, 64, 64, 2>(g, xp, wp, y, kh, stream);
+        if (form == kF64Block32) return launch_f64_mfma<Elem, 32, 32, 1>(g, xp, wp, y, kh, stream);
+        if (form == kF64Block64) return launch_f64_mfma<Elem, 64, 64, 2>(g, xp, wp, y, kh, stream);
         return launch_f64_mfma<Elem, 128, 32, 2>(g, xp, wp, y, kh, stream);
     }
     if (kh == 3)

@@ -1,10 +1,11 @@
-"""The launches of layers too large for one: the host arithmetic of
-launch_split.hpp, compiled and run on the CPU.  HIP takes fewer than 2^32
-work-items (gridDim.x * blockDim.x) along x."""
+"""The launches of layers too large for one, and the form that the float64
+convolution takes: the host arithmetic of launch_split.hpp, compiled and run on
+the CPU.  HIP takes fewer than 2^32 work-items (gridDim.x * blockDim.x) along x."""
 import subprocess
 
 import pytest
 
+import test_gpu_direct_f64 as F64
 from paper_1905_05233_amd import build_native as B
 
 SRC = r"""
@@ -23,7 +24,13 @@ int main(int argc, char** argv) {
         }
         return 0;
     }
-    for (int i = 1; i < argc; ++i) {
+    if (argc == 7) {   // pixels, C, K, taps, bytes of a value, compute units
+        int64_t a[6];
+        for (int i = 0; i < 6; ++i) a[i] = std::atoll(argv[1 + i]);
+        std::printf("%d\n", wg::f64_form(a[0], a[1], a[2], static_cast<int>(a[3]), a[4], static_cast<int>(a[5])));
+        return 0;
+    }
+    for (int i = 2; i < argc; ++i) {   // a word, then output channels, more than five of them
         const int64_t K = std::atoll(argv[i]), per = wg::output_tiles_per_launch(K);
         std::printf("%lld %lld %lld\n", (long long)per, (long long)(per * K),
                     (long long)(wg::output_blocks(per * K) * wg::kOutBlock));
@@ -42,7 +49,7 @@ def split(tmp_path_factory):
 
 def test_output_transform_launches_stay_within_the_grid(split):
     ks = [1, 3, 64, 255, 256, 257, 512, 4096, 65537, 0x7fffff00]
-    out = subprocess.run([split] + [str(k) for k in ks], capture_output=True, text=True, check=True).stdout
+    out = subprocess.run([split, "output"] + [str(k) for k in ks], capture_output=True, text=True, check=True).stdout
     for k, line in zip(ks, out.splitlines(), strict=True):
         per, pairs, items = map(int, line.split())
         assert per >= 1 and pairs < 2 ** 31, k       # ids of 31 bits
@@ -72,3 +79,23 @@ def test_input_transform_launches_reach_every_row(split, H, row, m):
         r1 = min(th, r0 + rows)
         assert (end - first) * row <= 1 << 30 and (r1 - r0) * thr < 2 ** 31
         assert first == max(0, r0 * m - 1) and end == min(H, r1 * m + 1)
+
+
+FORMS = ["one thread per output", "32 x 32", "64 x 64", "128 x 32"]
+
+
+def test_float64_shapes_reach_every_form(split):
+    """The shapes of the float64 tests select the forms that they name, and
+    together every form, with aligned runs of four values and without."""
+    seen = set()
+    cases = [(9, s, f) for s, f in F64.SHAPES + F64.SPECIAL] + [(3, s, f) for s, f in F64.SHAPES_1D]
+    for taps, (N, H, W, C, K), form in cases:
+        for es in (2, 4):
+            args = [N * H * W, C, K, taps, es, F64.CUS]
+            out = subprocess.run([split] + [str(v) for v in args], capture_output=True, text=True, check=True).stdout
+            assert FORMS[int(out)] == form, (taps, (N, H, W, C, K))
+        seen.add((taps, form, C % 4 == 0))
+    for taps in (9, 3):
+        assert {(taps, f, v4) for f in FORMS[1:] for v4 in (True, False)} <= seen
+    for form in FORMS[1:]:   # special values: every block shape
+        assert form in [f for _, f in F64.SPECIAL]
