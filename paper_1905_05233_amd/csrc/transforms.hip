@@ -6,8 +6,10 @@
 // consecutive channels of NHWC / channel-last buffers (coalesced).  The kernel
 // transform runs one thread per (domain row, kernel, channels), the input
 // transform one thread per (tile, channels) (input_regs.hpp), the output
-// transform one workgroup per (tile, 64 output channels) with its output rows
-// split over the waves.  The transform matrices arrive by value
+// transform one thread per (tile, output channel, group of output rows)
+// (output_regs.hpp) or, for layers of few such threads, one workgroup per (tile,
+// 64 output channels) with its output rows split over the waves.  The transform
+// matrices arrive by value
 // in the kernel-argument segment (uniform across the grid, so they live in
 // scalar registers); the small matrices are applied as two separable 1D passes
 // in fp32 registers with ascending-index fused multiply-adds, and results are

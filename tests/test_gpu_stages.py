@@ -88,14 +88,17 @@ def test_input_transform_bit_exact_random(spec, m, dtype, C):
 @pytest.mark.parametrize("spec,m,dtype,shape", [(WL.F4_A2P1, 4, "bf16", (3, 150, 170, 128)),
                                                  (WL.F6_TWO_QUAD, 6, "f16", (6, 170, 160, 128)),
                                                  (WL.F4_LINEAR, 4, "f32", (3, 150, 170, 128))])
-def test_input_transform_walking_instance_bit_exact_random(spec, m, dtype, shape):
-    """The instance whose workgroups walk four tiles (built-in plans, layers
-    of 8192 or more (tile, 64-channel) units, a ragged last workgroup) on
-    random data: V equal to the oracle bit for bit."""
+def test_input_transform_large_layer_bit_exact_random(spec, m, dtype, shape):
+    """Built-in plans on layers of many workgroups: pairs of channels (the last
+    workgroup half filled), single channels with unsplit domain rows, and single
+    channels in fp32.  V equal to the oracle bit for bit on random data."""
     p, op = _plan(spec, m, dtype)
     N, H, W, C = shape
     T = N * (-(-H // m)) * (-(-W // m))
-    assert T * (-(-C // 64)) >= 8192 and T % 4 != 0
+    pairs = dtype != "f32" and m <= 4
+    threads = T * C // (2 if pairs else 1)
+    # one channel per thread up to 2^16 of them, rows split up to 2^15
+    assert T * C > 1 << 16 and threads > 1 << 15
     x, _ = WL.draw_inputs(N, H, W, C, 1, "halfnormal", seed=H + C)
     x = OF.to_dtype(x, dtype)
     V = to_np(p.input_transform(to_dev(x, dtype)))
