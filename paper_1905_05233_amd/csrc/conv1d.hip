@@ -22,6 +22,7 @@
 
 #include "device_common.hpp"
 #include "kernels.hpp"
+#include "launch_split.hpp"
 
 namespace wg {
 
@@ -131,8 +132,6 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
 
-constexpr int k1dWaves = 8;
-constexpr int k1dChunk = 64;             // bytes of a channel row per step
 constexpr int k1dTiles = 64;             // most tiles of a block
 constexpr int k1dMaxAlpha = 10;
 
@@ -392,16 +391,7 @@ hipError_t launch_output_transform_1d_t(const Geometry& g, const OutputTable& ta
     return hipGetLastError();
 }
 
-// The fused kernel walks a row's chunks one after another, so a layer with long
-// rows and few blocks is faster through the separate kernels, which spread the
-// points over the chip: 1x100, 512 -> 512 in bf16 (4 blocks, 16 chunks) 40
-// against 21 us, 8x512, 512 -> 512 (128 blocks) 42 against 40 us, and the other
-// way 32x512, 512 -> 512 (512 blocks) 69 against 89 us, 4x2048, 128 -> 128 (64
-// blocks, 4 chunks) 16 against 24 us, 3x6542, 16 -> 16 (one chunk) 6 against 16 us.
-constexpr int64_t k1dFewPoints = 20;    // chunks x alpha' that one block may walk anyway
-constexpr int64_t k1dBlocksPerChunk = 14;
-
-// It takes the (tile, alpha') shapes of the compiled 2D transforms up to ten
+// The fused kernel takes the (tile, alpha') shapes of the compiled 2D transforms up to ten
 // points (in fp32 thirteen took 70 against 64 us for 32x2000, 64 -> 64: the
 // points' sums fill the registers), inputs within 1 GiB and planes of U within
 // 32-bit offsets.
@@ -415,10 +405,7 @@ bool conv1d_fused_supported_t(const Geometry& g) {
 template <int D>
 bool conv1d_fused_chosen_t(const Geometry& g) {
     if (!conv1d_fused_supported_t<D>(g)) return false;
-    const int64_t chunks = (g.Cp * (D == 0 ? 4 : 2) + k1dChunk - 1) / k1dChunk;
-    const int64_t kw = g.K > 64 ? 8 : 4, n_tiles = 32 * (k1dWaves / kw);
-    const int64_t blocks = (g.T + n_tiles - 1) / n_tiles * ((g.K + 16 * kw - 1) / (16 * kw));
-    return chunks * g.alpha <= k1dFewPoints || blocks >= k1dBlocksPerChunk * chunks;
+    return conv1d_one_kernel_pays(g.T, g.Cp, g.K, g.Kp, g.alpha, D == 0 ? 4 : 2);
 }
 
 template <int D>
@@ -430,13 +417,12 @@ hipError_t launch_conv1d_fused_t(const Geometry& g, const InputTable& itab, cons
     Map1d mp;
     mp.tl = make_fastdiv(g.tw);
     mp.xbytes = static_cast<uint32_t>(g.N * g.W * g.C * es);
-    mp.kw = g.K > 64 ? 8 : 4;
-    mp.n_kb = static_cast<int>((g.K + 16 * mp.kw - 1) / (16 * mp.kw));
+    mp.kw = conv1d_waves_k(g.K);
+    mp.n_kb = static_cast<int>(conv1d_k_blocks(g.K));
     mp.rb = static_cast<int>(g.Cp * es);
-    mp.n_chunks = (mp.rb + k1dChunk - 1) / k1dChunk;
+    mp.n_chunks = static_cast<int>(conv1d_chunks(g.Cp, es));
     mp.plane_u = static_cast<int>(g.K * g.Cp * es);
-    const int64_t n_tiles = 32 * (k1dWaves / mp.kw);
-    const int64_t blocks = (g.T + n_tiles - 1) / n_tiles * mp.n_kb;
+    const int64_t blocks = conv1d_blocks(g.T, g.K);
     if (blocks > 0x7fffffff) return hipErrorInvalidValue;
 #define WG_1D_CASE(TT, A)                                                                                         \
     if constexpr (A <= k1dMaxAlpha)                                                                               \

@@ -1,5 +1,5 @@
-"""The launches of layers too large for one, and the form that the float64
-convolution takes: the host arithmetic of launch_split.hpp, compiled and run on
+"""The launches of layers too large for one, and the forms that the 1D and the
+float64 convolution take: the host arithmetic of launch_split.hpp, compiled and run on
 the CPU.  HIP takes fewer than 2^32 work-items (gridDim.x * blockDim.x) along x."""
 import subprocess
 
@@ -22,6 +22,12 @@ int main(int argc, char** argv) {
             const wg::InputBand b = wg::input_band(a[0], r0, std::min(s.rows, a[2] - r0), static_cast<int>(a[4]));
             std::printf("%lld %lld %lld\n", (long long)r0, (long long)b.first, (long long)b.end);
         }
+        return 0;
+    }
+    if (argc == 9) {   // tiles, Cp, K, Kp, alpha', bytes of a value, two words
+        int64_t a[6];
+        for (int i = 0; i < 6; ++i) a[i] = std::atoll(argv[1 + i]);
+        std::printf("%d\n", wg::conv1d_one_kernel_pays(a[0], a[1], a[2], a[3], static_cast<int>(a[4]), a[5]));
         return 0;
     }
     if (argc == 7) {   // pixels, C, K, taps, bytes of a value, compute units
@@ -79,6 +85,31 @@ def test_input_transform_launches_reach_every_row(split, H, row, m):
         r1 = min(th, r0 + rows)
         assert (end - first) * row <= 1 << 30 and (r1 - r0) * thr < 2 ** 31
         assert first == max(0, r0 * m - 1) and end == min(H, r1 * m + 1)
+
+
+@pytest.mark.parametrize("m,alpha,es,layer,one_kernel", [
+    # N, L, C, K and both times in us, one kernel and separate
+    (4, 7, 2, (16, 4096, 128, 128), True),     # 26, 87
+    (4, 7, 4, (16, 4096, 64, 128), True),      # a fifth of the separate kernels' bytes
+    (4, 7, 2, (3, 6542, 16, 16), True),        # 6, 16: one chunk
+    (4, 7, 2, (1, 100, 512, 512), False),      # 40, 21: four blocks
+    (4, 7, 2, (32, 512, 512, 512), True),      # 69, 89
+    (6, 10, 4, (5, 8000, 128, 512), False),    # 173, 146
+    (6, 10, 4, (16, 4096, 512, 512), False),   # 901, 633
+    (6, 10, 2, (64, 300, 512, 1024), False),   # 258, 140
+    (6, 10, 2, (32, 8000, 301, 77), True),     # 334, 388
+    (4, 6, 4, (64, 300, 512, 512), False),     # 270, 200
+    (2, 4, 4, (4, 8000, 256, 128), True),      # 0.67 of the separate kernels' time
+    # the layers of the GPU tests of both forms
+    (4, 7, 2, (1, 257, 8, 65), True), (4, 7, 4, (40, 130, 34, 66), True), (4, 6, 2, (1, 40, 200, 20), False),
+    (6, 10, 2, (60, 100, 48, 40), True), (4, 7, 2, (1400, 41, 200, 20), True), (4, 7, 4, (1400, 41, 201, 70), True),
+    (4, 7, 2, (1, 41, 200, 20), False), (4, 7, 4, (1, 41, 201, 70), False),
+], ids=str)
+def test_1d_form_of_a_layer(split, m, alpha, es, layer, one_kernel):
+    N, L, C, K = layer
+    args = [N * -(-L // m), -(-C // 8) * 8, K, -(-K // 8) * 8, alpha, es, "1d", "form"]
+    out = subprocess.run([split] + [str(v) for v in args], capture_output=True, text=True, check=True).stdout
+    assert bool(int(out)) == one_kernel
 
 
 FORMS = ["one thread per output", "32 x 32", "64 x 64", "128 x 32"]
