@@ -13,17 +13,18 @@ namespace wg {
 constexpr int64_t kMaxWorkItems = 0xffffffff;
 
 // Output transform in registers: workgroups of kOutBlock (tile, channel) pairs,
-// kOutGroups of them (row groups) for the same pairs.
+// `groups` of them (row groups, kOutGroups at most) for the same pairs.
 constexpr int kOutBlock = 256;
 constexpr int kOutGroups = 2;
 // Most pairs of a launch: ids below 2^31, and the row groups' workgroups within
 // kMaxWorkItems.
-constexpr int64_t kOutMaxPairs =
-    std::min<int64_t>(0x7fffffff, kMaxWorkItems / kOutGroups) / kOutBlock * kOutBlock;
-// Whole tiles of one launch for K output channels (K at most kOutMaxPairs), and
+constexpr int64_t output_max_pairs(int groups) {
+    return std::min<int64_t>(0x7fffffff, kMaxWorkItems / groups) / kOutBlock * kOutBlock;
+}
+// Whole tiles of one launch for K output channels (K at most output_max_pairs), and
 // its workgroups for `pairs` pairs.
-constexpr int64_t output_tiles_per_launch(int64_t K) { return kOutMaxPairs / K; }
-constexpr int64_t output_blocks(int64_t pairs) { return (pairs + kOutBlock - 1) / kOutBlock * kOutGroups; }
+constexpr int64_t output_tiles_per_launch(int64_t K, int groups) { return output_max_pairs(groups) / K; }
+constexpr int64_t output_blocks(int64_t pairs, int groups) { return (pairs + kOutBlock - 1) / kOutBlock * groups; }
 
 // Input transform in registers: 32-bit offsets into the pixels that a launch
 // reads, at most kInMaxBytes of them (below the out-of-range offsets that its

@@ -25,7 +25,7 @@ namespace wg {
 
 struct OutputMap {
     FastDiv per_tile, tw, th;   // divisors: threads per tile, tiles per row, tile rows
-    int64_t threads;            // (tile, channel) pairs of this launch (at most kOutMaxPairs)
+    int64_t threads;            // (tile, channel) pairs of this launch (at most output_max_pairs)
     int64_t tile0;              // its first tile
 };
 
@@ -66,14 +66,14 @@ __device__ __forceinline__ void output_regs_rows(const OutputTable& tab, const f
     }
 }
 
-template <typename Elem, int MM, int ALPHA, class CO>
+template <typename Elem, int MM, int ALPHA, class CO, int kG>
 __global__ __launch_bounds__(kOutBlock) void output_transform_regs(OutputTable tab, const float* __restrict__ Mx,
                                                               Elem* __restrict__ y, Geometry geo, OutputMap mp) {
     const int64_t bid = blockIdx.x, G = gridDim.x;
     const int64_t xcd = bid % 8;
     const int64_t unit = xcd * (G / 8) + (xcd < G % 8 ? xcd : G % 8) + bid / 8;   // XCD-aware, as the input transform
-    const int group = static_cast<int>(unit % kOutGroups);
-    const int64_t gid = unit / kOutGroups * kOutBlock + threadIdx.x;
+    const int group = static_cast<int>(unit % kG);
+    const int64_t gid = unit / kG * kOutBlock + threadIdx.x;
     if (gid >= mp.threads) return;
     const uint32_t tl = fast_div(static_cast<uint32_t>(gid), mp.per_tile);
     const int64_t k = static_cast<int64_t>(static_cast<uint32_t>(gid) - tl * mp.per_tile.d);
@@ -85,9 +85,10 @@ __global__ __launch_bounds__(kOutBlock) void output_transform_regs(OutputTable t
     const float* in = Mx + tile * geo.Kp + k;
     Elem* yk = y + static_cast<int64_t>(n) * geo.H * geo.W * geo.K + k;
     const int64_t plane = geo.T * geo.Kp, hr0 = static_cast<int64_t>(ty) * MM, wc0 = static_cast<int64_t>(tx) * MM;
-    constexpr int kR = (MM + kOutGroups - 1) / kOutGroups;
+    constexpr int kR = (MM + kG - 1) / kG;
     if (group == 0) output_regs_rows<Elem, MM, ALPHA, CO, 0, kR>(tab, in, plane, yk, hr0, wc0, geo);
-    else output_regs_rows<Elem, MM, ALPHA, CO, kR, MM>(tab, in, plane, yk, hr0, wc0, geo);
+    if constexpr (kR < MM)
+        if (group != 0) output_regs_rows<Elem, MM, ALPHA, CO, kR, MM>(tab, in, plane, yk, hr0, wc0, geo);
 }
 
 }  // namespace wg

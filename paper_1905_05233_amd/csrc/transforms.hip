@@ -276,6 +276,11 @@ constexpr int output_rows_per_wave(int alpha) { return alpha >= 9 ? 3 : 2; }
 // (1x14x14x512 in bf16 has 8 thousand; 6x75x91x120 in fp16, 315 thousand, 17.4 us
 // here and 12.3 there; 32x28x28x512 28.0 and 26.7).
 constexpr int64_t kOutManyThreads = int64_t(1) << 17;
+// Bytes of M up to which 2x2 tiles take two row groups as well, one row each: the
+// second group's reads hit the 256 MB last-level cache.  alpha' = 5 in bf16, two
+// groups and one: 32x28x28x256 (161 MB) 24.5 and 25.9 us, 4x112x112x256 (321 MB) 70.9
+// and 65.2.  Larger tiles read M twice for half of their rows each.
+constexpr int64_t kOutCachedBytes = int64_t(256) << 20;
 
 template <int MM, int ALPHA>
 struct OutputShape {
@@ -509,24 +514,31 @@ hipError_t launch_in(const Geometry& g, const KernelTable* ktab, const InputTabl
     return hipSuccess;
 }
 
+template <typename Elem, int TT, int A, class CO, int G>
+hipError_t launch_ot_regs(const Geometry& g, const OutputTable& tab, const float* M, Elem* yp, hipStream_t stream) {
+    // launches of whole tiles (one but for huge layers)
+    OutputMap mp;
+    mp.per_tile = make_fastdiv(g.K);
+    mp.tw = make_fastdiv(g.tw);
+    mp.th = make_fastdiv(g.th);
+    const int64_t per = output_tiles_per_launch(g.K, G);
+    for (int64_t t0 = 0; t0 < g.T; t0 += per) {
+        mp.tile0 = t0;
+        mp.threads = std::min<int64_t>(per, g.T - t0) * g.K;
+        hipLaunchKernelGGL((output_transform_regs<Elem, TT - 2, A, CO, G>),
+                           dim3(static_cast<unsigned>(output_blocks(mp.threads, G))), dim3(kOutBlock), 0, stream, tab, M, yp, g, mp);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
+}
+
 template <typename Elem, int TT, int A, class CO>
 hipError_t launch_ot(const Geometry& g, const OutputTable& tab, const float* M, Elem* yp, hipStream_t stream) {
-    if (g.T * g.K >= kOutManyThreads && g.T < (int64_t(1) << 31) && g.K <= kOutMaxPairs) {
-        // launches of whole tiles (one but for huge layers)
-        OutputMap mp;
-        mp.per_tile = make_fastdiv(g.K);
-        mp.tw = make_fastdiv(g.tw);
-        mp.th = make_fastdiv(g.th);
-        const int64_t per = output_tiles_per_launch(g.K);
-        for (int64_t t0 = 0; t0 < g.T; t0 += per) {
-            mp.tile0 = t0;
-            mp.threads = std::min<int64_t>(per, g.T - t0) * g.K;
-            hipLaunchKernelGGL((output_transform_regs<Elem, TT - 2, A, CO>),
-                               dim3(static_cast<unsigned>(output_blocks(mp.threads))), dim3(kOutBlock), 0, stream, tab, M, yp, g, mp);
-            const hipError_t e = hipGetLastError();
-            if (e != hipSuccess) return e;
-        }
-        return hipSuccess;
+    if (g.T * g.K >= kOutManyThreads && g.T < (int64_t(1) << 31) && g.K <= output_max_pairs(kOutGroups)) {
+        if constexpr (TT == 4)
+            if (int64_t(A) * A * g.T * g.Kp * 4 > kOutCachedBytes) return launch_ot_regs<Elem, TT, A, CO, 1>(g, tab, M, yp, stream);
+        return launch_ot_regs<Elem, TT, A, CO, kOutGroups>(g, tab, M, yp, stream);
     }
     const int64_t units = g.T * ((g.K + kOutCh - 1) / kOutCh);
     if (units > 0x7fffffff) return hipErrorInvalidValue;

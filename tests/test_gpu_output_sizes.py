@@ -20,6 +20,7 @@ pytestmark = pytest.mark.gpu
     (WL.F6_TWO_QUAD, 6, (16, 50, 55, 130)),
     ("0,-1,1,-1/2,inf", 3, (10, 70, 71, 25)),    # odd tiles: groups of two rows and one
     ("0,-1,1,-1/2,2,1/2,-2,a^2+1,inf", 8, (20, 64, 60, 108)),
+    ("0,a^2+1,inf", 2, (30, 57, 35, 250)),       # M of 382 MiB: one row group
 ], ids=str)
 def test_output_transform_forms_agree(spec, m, shape, dtype):
     from paper_1905_05233_amd.winograd import Plan

@@ -36,10 +36,11 @@ int main(int argc, char** argv) {
         std::printf("%d\n", wg::f64_form(a[0], a[1], a[2], static_cast<int>(a[3]), a[4], static_cast<int>(a[5])));
         return 0;
     }
-    for (int i = 2; i < argc; ++i) {   // a word, then output channels, more than five of them
-        const int64_t K = std::atoll(argv[i]), per = wg::output_tiles_per_launch(K);
+    const int groups = std::atoi(argv[1]);
+    for (int i = 2; i < argc; ++i) {   // row groups, then output channels, more than eight of them
+        const int64_t K = std::atoll(argv[i]), per = wg::output_tiles_per_launch(K, groups);
         std::printf("%lld %lld %lld\n", (long long)per, (long long)(per * K),
-                    (long long)(wg::output_blocks(per * K) * wg::kOutBlock));
+                    (long long)(wg::output_blocks(per * K, groups) * wg::kOutBlock));
     }
 }
 """
@@ -53,14 +54,15 @@ def split(tmp_path_factory):
     return str(d / "split")
 
 
-def test_output_transform_launches_stay_within_the_grid(split):
+@pytest.mark.parametrize("groups", [1, 2])
+def test_output_transform_launches_stay_within_the_grid(split, groups):
     ks = [1, 3, 64, 255, 256, 257, 512, 4096, 65537, 0x7fffff00]
-    out = subprocess.run([split, "output"] + [str(k) for k in ks], capture_output=True, text=True, check=True).stdout
+    out = subprocess.run([split, str(groups)] + [str(k) for k in ks], capture_output=True, text=True, check=True).stdout
     for k, line in zip(ks, out.splitlines(), strict=True):
         per, pairs, items = map(int, line.split())
         assert per >= 1 and pairs < 2 ** 31, k       # ids of 31 bits
         assert pairs > 2 ** 31 - 256 - k, k          # and as many tiles as fit
-        assert 2 * pairs <= items < 2 ** 32, k       # two row groups
+        assert groups * pairs <= items < 2 ** 32, k
 
 
 @pytest.mark.parametrize("m", [2, 4, 7, 12])
