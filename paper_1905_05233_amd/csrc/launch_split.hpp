@@ -28,21 +28,28 @@ constexpr int64_t output_blocks(int64_t pairs, int groups) { return (pairs + kOu
 
 // Input transform in registers: 32-bit offsets into the pixels that a launch
 // reads, at most kInMaxBytes of them (below the out-of-range offsets that its
-// kernel uses), and thread ids below 2^31.
+// kernel uses), thread ids below 2^31, and the row groups' workgroups within
+// kMaxWorkItems.
 constexpr int kInBlock = 256;
 constexpr int64_t kInMaxBytes = int64_t(1) << 30;
+constexpr int64_t input_max_threads(int groups) {
+    return std::min<int64_t>(0x7fffffff, kMaxWorkItems / groups / kInBlock * kInBlock);
+}
+constexpr int64_t input_blocks(int64_t threads, int groups) { return (threads + kInBlock - 1) / kInBlock * groups; }
 // What one launch covers: `images` whole images, or, where one image is too
 // large, `rows` tile rows of one.  rows = 0: not even one tile row fits.
 struct InputSplit {
     int64_t images, rows;
 };
-// row_bytes: of a row of pixels; tile_row_threads: threads of a row of tiles.
-constexpr InputSplit input_split(int64_t H, int64_t row_bytes, int64_t tile_rows, int64_t tile_row_threads, int m) {
-    const int64_t img_bytes = H * row_bytes, img_threads = tile_rows * tile_row_threads;
-    if (img_bytes <= kInMaxBytes && img_threads <= 0x7fffffff)
-        return {std::min<int64_t>(kInMaxBytes / img_bytes, 0x7fffffff / img_threads), tile_rows};
+// row_bytes: of a row of pixels; tile_row_threads: threads of a row of tiles;
+// groups: the row groups of layers of any size.
+constexpr InputSplit input_split(int64_t H, int64_t row_bytes, int64_t tile_rows, int64_t tile_row_threads, int m,
+                                 int groups) {
+    const int64_t img_bytes = H * row_bytes, img_threads = tile_rows * tile_row_threads, most = input_max_threads(groups);
+    if (img_bytes <= kInMaxBytes && img_threads <= most)
+        return {std::min<int64_t>(kInMaxBytes / img_bytes, most / img_threads), tile_rows};
     // r tile rows read at most r m + 2 rows of pixels
-    const int64_t rows = std::min<int64_t>((kInMaxBytes / row_bytes - 2) / m, 0x7fffffff / tile_row_threads);
+    const int64_t rows = std::min<int64_t>((kInMaxBytes / row_bytes - 2) / m, most / tile_row_threads);
     return {1, std::max<int64_t>(0, std::min(rows, tile_rows))};
 }
 // The rows of pixels that tile rows r0 .. r0 + rows - 1 read: [first, end).

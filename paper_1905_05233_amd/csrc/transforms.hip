@@ -213,7 +213,26 @@ template <typename Elem> constexpr bool input_pairs(int tt) { return sizeof(Elem
 // the window.  It pays while the layer has too few threads to occupy the
 // SIMDs: 4x56x56x64 in fp32 with 8x8 tiles (12.5 thousand threads) 10.6 -> 6.8
 // us, while 16x28x28x256 with 6x6 tiles (102 thousand) went from 8.1 to 9.4 us.
+//
+// Windows of 12 and more with alpha' over 12, and 10x10 ones with alpha' = 12,
+// split at every size: with all rows in one thread the coefficients overflow the
+// scalar registers, and the code (60 KB for the latter, 120 - 266 KB for the
+// others) the instruction cache; a group's part of it fits.  221 thousand threads
+// in bf16, all rows -> split: t = 10, alpha' = 12 64 -> 39 us; 12, 13 126 -> 84;
+// 12, 15 164 -> 88; 14, 14 228 -> 109; 14, 16 334 -> 135.  The others have at most
+// 39 KB, and lose: 12x12 with alpha' = 12 49 -> 55, 10x10 with alpha' = 13 41 -> 64.
+//
+// 14x14 windows in 16 bits take two rows a group up to alpha' = 15: with four the
+// window and the rows' sums need 320 registers, one wave per SIMD (221 thousand
+// threads, alpha' = 14: four rows 132 us, two 109; alpha' = 16: 135 and 145).  Those
+// and the fp32 ones come within a few registers of two waves per SIMD, so they are
+// held to it.
 constexpr int kInGroups = 4;
+constexpr int input_groups(int tt, int alpha, int es) {
+    return tt >= 14 && es == 2 && alpha <= 15 ? (alpha + 1) / 2 : tt >= 8 ? kInGroups : 1;
+}
+constexpr bool input_always_split(int tt, int alpha) { return tt >= 12 ? alpha > 12 : tt == 10 && alpha == 12; }
+constexpr int input_waves(int tt, int groups, int es) { return tt >= 14 && (es == 4 || groups > kInGroups) ? 2 : 1; }
 constexpr int64_t kInFewThreads = int64_t(1) << 15;
 // Layers of at most one workgroup of one-channel threads per CU are bound by one
 // thread's latency: they take one channel per thread, and in the joint launch
@@ -223,10 +242,9 @@ constexpr int64_t kInFewThreads = int64_t(1) << 15;
 // 1x28x28, 256 -> 256 5.15 -> 4.99 -> 4.33, 4x14x14, 512 -> 32 4.79 -> 4.42 -> 3.74.
 // With more units the short kernel transform stays ahead.
 constexpr int64_t kInFirstUnits = 256;
-constexpr int input_groups(int tt) { return tt >= 8 ? kInGroups : 1; }
 
 template <typename Elem, int TT, int ALPHA, class CO, int VEC, int RG, bool BIG, bool RELU>
-__global__ __launch_bounds__(kInBlock) void input_transform(InputTable tab, const Elem* __restrict__ x,
+__global__ __launch_bounds__(kInBlock, (input_waves(TT, RG, sizeof(Elem)))) void input_transform(InputTable tab, const Elem* __restrict__ x,
                                                             unsigned char* __restrict__ V, Geometry geo, InputMap mp) {
     input_regs_unit<Elem, TT, ALPHA, CO, VEC, RG, BIG, RELU>(tab, x, V, geo, mp, blockIdx.x, gridDim.x);
 }
@@ -407,7 +425,8 @@ hipError_t launch_in(const Geometry& g, const KernelTable* ktab, const InputTabl
     constexpr int ES = static_cast<int>(sizeof(Elem));
     constexpr int kM = TT - 2;
     constexpr bool kPairs = input_pairs<Elem>(TT);
-    constexpr int kRG = input_groups(TT);
+    constexpr int kRG = input_groups(TT, A, ES);
+    constexpr int kBigRG = input_always_split(TT, A) ? kRG : 1;   // row groups of layers of any size
     const bool few = g.T * g.Cp <= kInFirstUnits * kInBlock;
     const bool pairs = kPairs && g.C % 2 == 0 && !few;
     const int vec = pairs ? 2 : 1;
@@ -416,7 +435,7 @@ hipError_t launch_in(const Geometry& g, const KernelTable* ktab, const InputTabl
     mp.per_tile = make_fastdiv(g.Cp / vec);
     mp.tw = make_fastdiv(g.tw);
     mp.plane = g.T * g.Cp * ES;
-    const InputSplit sp = input_split(g.H, row * ES, g.th, thr_row, kM);
+    const InputSplit sp = input_split(g.H, row * ES, g.th, thr_row, kM, kBigRG);
     if (sp.rows == 0) {
         // rows of over kInMaxBytes / t: the kernel transform apart, 64-bit addresses
         if constexpr (RELU) {
@@ -426,7 +445,7 @@ hipError_t launch_in(const Geometry& g, const KernelTable* ktab, const InputTabl
             mp.threads = g.T * (g.Cp / vec);
             mp.xbytes = 0;
             mp.h = mp.up = 0;
-            const int64_t blocks = (mp.threads + kInBlock - 1) / kInBlock;
+            const int64_t blocks = input_blocks(mp.threads, kBigRG);
             if (blocks * kInBlock > kMaxWorkItems) return hipErrorInvalidValue;
             if (ktab) {
                 constexpr int D = sizeof(Elem) == 4 ? 0 : __is_same(Elem, bf16_t) ? 2 : 1;
@@ -434,7 +453,7 @@ hipError_t launch_in(const Geometry& g, const KernelTable* ktab, const InputTabl
                 if (e != hipSuccess) return e;
             }
 #define WG_IT_BIG(VEC)                                                                                             \
-    hipLaunchKernelGGL((input_transform<Elem, TT, A, CO, VEC, 1, true, false>), dim3(static_cast<unsigned>(blocks)), \
+    hipLaunchKernelGGL((input_transform<Elem, TT, A, CO, VEC, kBigRG, true, false>), dim3(static_cast<unsigned>(blocks)), \
                        dim3(kInBlock), 0, stream, tab, xp, reinterpret_cast<unsigned char*>(vp), g, mp)
             if constexpr (kPairs) {
                 if (pairs) WG_IT_BIG(2);
@@ -459,8 +478,8 @@ hipError_t launch_in(const Geometry& g, const KernelTable* ktab, const InputTabl
         mp.xbytes = static_cast<uint32_t>(nn * mp.h * row * ES);
         const Elem* xs = xp + n0 * x_img + band.first * row;
         auto* vs = reinterpret_cast<unsigned char*>(vp) + (n0 * tiles_img + r0 * g.tw) * g.Cp * ES;
-        const bool split = kRG > 1 && mp.threads <= kInFewThreads;
-        const int64_t units = (mp.threads + kInBlock - 1) / kInBlock * (split ? kRG : 1);
+        const bool split = kBigRG > 1 || (kRG > 1 && mp.threads <= kInFewThreads);
+        const int64_t units = input_blocks(mp.threads, split ? kRG : 1);
         if (ktab && first) {
             // the kernel transform's workgroups, a multiple of 8, so the input
             // transform's ids keep their XCD (id mod 8).  One thread for every
@@ -499,7 +518,7 @@ hipError_t launch_in(const Geometry& g, const KernelTable* ktab, const InputTabl
                 else WG_IT(1, 1);
             } else {
                 if (split) WG_IT(1, kRG);
-                else WG_IT(1, 1);
+                else WG_IT(1, kBigRG);
             }
 #undef WG_IT
         }

@@ -18,6 +18,9 @@ from paper_1905_05233_amd import workloads as WL
 pytestmark = pytest.mark.gpu
 
 F8 = ("0,-1,1,-1/2,2,1/2,-2,a^2+1,inf", 8)
+F8A12 = ("0,-1,1,-1/2,2,a^2+1,a^2-2,inf", 8)
+F10 = ("0,-1,1,-1/2,2,1/2,-2,-1/4,4,a^2+1,inf", 10)
+F12 = ("0,-1,1,-1/2,2,1/2,-2,-1/4,4,1/4,-4,a^2+1,inf", 12)
 
 
 @pytest.mark.parametrize("spec,m,dtype,shape", [
@@ -34,6 +37,11 @@ F8 = ("0,-1,1,-1/2,2,1/2,-2,a^2+1,inf", 8)
     (WL.F6_TWO_QUAD, 6, "f32", (1, 96, 97, 128)),  # just above: not split
     (WL.F6_LINEAR, 6, "bf16", (1, 20, 20, 40)),   # split, 8 domain rows: two a group
     (F8[0], F8[1], "f16", (1, 30, 22, 23)),       # split, 11 domain rows: the last group has two
+    (F8[0], F8[1], "bf16", (2, 90, 88, 130)),     # 10x10 windows above 2^15 threads: not split
+    (F8A12[0], F8A12[1], "f32", (2, 90, 88, 130)),  # alpha' = 12: split
+    (F10[0], F10[1], "bf16", (2, 115, 110, 130)),  # 12x12, 13 domain rows: split, the last group has one
+    (F12[0], F12[1], "bf16", (2, 136, 130, 130)),  # 14x14, 15 domain rows: two a group, the last has one
+    (F12[0], F12[1], "f32", (2, 136, 130, 130)),   # four a group, the last has three
 ], ids=str)
 def test_input_transform_launch_forms(spec, m, dtype, shape):
     from paper_1905_05233_amd.winograd import Plan

@@ -13,10 +13,13 @@ SRC = r"""
 #include <cstdlib>
 #include "launch_split.hpp"
 int main(int argc, char** argv) {
-    if (argc == 6) {   // H, bytes of a row of pixels, tile rows, threads of a row of tiles, m
-        int64_t a[5];
-        for (int i = 0; i < 5; ++i) a[i] = std::atoll(argv[1 + i]);
-        const wg::InputSplit s = wg::input_split(a[0], a[1], a[2], a[3], static_cast<int>(a[4]));
+    if (argc == 8) {   // H, bytes of a row of pixels, tile rows, threads of a row of tiles, m, row groups, a word
+        int64_t a[6];
+        for (int i = 0; i < 6; ++i) a[i] = std::atoll(argv[1 + i]);
+        const int groups = static_cast<int>(a[5]);
+        const wg::InputSplit s = wg::input_split(a[0], a[1], a[2], a[3], static_cast<int>(a[4]), groups);
+        const int64_t threads = std::max<int64_t>(s.images, 1) * s.rows * a[3];
+        std::printf("%lld %lld\n", (long long)threads, (long long)(wg::input_blocks(threads, groups) * wg::kInBlock));
         std::printf("%lld %lld\n", (long long)s.images, (long long)s.rows);
         for (int64_t r0 = 0; s.rows && s.rows < a[2] && r0 < a[2]; r0 += s.rows) {
             const wg::InputBand b = wg::input_band(a[0], r0, std::min(s.rows, a[2] - r0), static_cast<int>(a[4]));
@@ -65,27 +68,31 @@ def test_output_transform_launches_stay_within_the_grid(split, groups):
         assert groups * pairs <= items < 2 ** 32, k
 
 
-@pytest.mark.parametrize("m", [2, 4, 7, 12])
+@pytest.mark.parametrize("m,groups", [(2, 1), (4, 1), (7, 1), (8, 4), (12, 4)])
 @pytest.mark.parametrize("H,row", [(16, 1 << 20), (1024, 1 << 20), (1025, 1 << 20), (1 << 14, (1 << 17) + 2),
                                    (300, (1 << 26) - 6), (9, 1 << 28), (3, 1 << 29), (1, 1 << 30), (1, (1 << 30) + 4),
                                    (1 << 29, 2), (1 << 30, 2)])
-def test_input_transform_launches_reach_every_row(split, H, row, m):
+def test_input_transform_launches_reach_every_row(split, H, row, m, groups):
     """Groups of images or bands of tile rows: the bytes and ids of each within
     32-bit reach, and every pixel that a band's tiles read among its rows."""
     th, thr = -(-H // m), 8 * max(1, row // 64)
-    out = subprocess.run([split] + [str(v) for v in (H, row, th, thr, m)], capture_output=True, text=True, check=True).stdout
-    (images, rows), *bands = [tuple(map(int, line.split())) for line in out.splitlines()]
-    if H * row <= 1 << 30 and th * thr < 2 ** 31:
-        assert rows == th and images >= 1 and images * H * row <= 1 << 30 and images * th * thr < 2 ** 31
+    args = [split] + [str(v) for v in (H, row, th, thr, m, groups)] + ["input"]
+    out = subprocess.run(args, capture_output=True, text=True, check=True).stdout
+    (threads, items), (images, rows), *bands = [tuple(map(int, line.split())) for line in out.splitlines()]
+    assert threads < 2 ** 31 and threads * groups <= items < 2 ** 32
+    most = min(2 ** 31 - 1, (2 ** 32 - 1) // groups // 256 * 256)
+    if H * row <= 1 << 30 and th * thr <= most:
+        assert rows == th and images >= 1 and images * H * row <= 1 << 30
+        assert (images + 1) * H * row > 1 << 30 or (images + 1) * th * thr > most
         return
     assert images == 1
     if rows == 0:
-        assert (m + 2) * row > 1 << 30 or thr >= 2 ** 31
+        assert (m + 2) * row > 1 << 30 or thr > most
         return
     assert rows < th and len(bands) == -(-th // rows)
     for r0, first, end in bands:
         r1 = min(th, r0 + rows)
-        assert (end - first) * row <= 1 << 30 and (r1 - r0) * thr < 2 ** 31
+        assert (end - first) * row <= 1 << 30 and (r1 - r0) * thr <= most
         assert first == max(0, r0 * m - 1) and end == min(H, r1 * m + 1)
 
 
