@@ -31,13 +31,19 @@ namespace wg {
 
 // What a launch of the register form covers: whole images, or a band of tile
 // rows of one image (launch_split.hpp).
+// The geometry that it gets has the rows of pixels of an image or the band as H.
 struct InputMap {
     FastDiv per_tile, tw, th;   // divisors: threads per tile, tiles per row, tile rows of an image or the band
     int64_t threads;            // (tile, run) pairs of this launch
     uint32_t xbytes;            // bytes of its pixels (at most kInMaxBytes)
-    int h, up;                  // rows of pixels of an image or the band; the first window row is row -up of them
     int64_t plane;              // bytes of a plane of V (all images)
 };
+// kInTop: whole images, or the band at the top of one; its first window row is the
+// padding above it.  kInBelow: a band below, whose first window row is its first row
+// of pixels (apart from kInTop because a run-time row was enough to make the code of
+// 10x10 windows with alpha' = 10 in fp32 spill: 221 thousand threads 28 -> 39 us).
+// kInFar: 64-bit addresses.
+enum InputPart { kInTop, kInBelow, kInFar };
 
 // VEC: channels per thread (2: 4-byte accesses of 16-bit pairs, C even; 1: one channel)
 template <typename Elem, int VEC> struct InRun;
@@ -155,7 +161,7 @@ __device__ __forceinline__ void input_regs_groups(const InputTable& tab, const t
 // 32-bit offsets through a buffer descriptor (at most kInMaxBytes of pixels); a
 // row or column outside the image gets an offset past every record, so its
 // loads return zero without a branch (valid sums stay below 2^30).
-template <typename Elem, int TT, int VEC>
+template <typename Elem, int TT, int VEC, InputPart PART>
 __device__ __forceinline__ void input_window(const Elem* __restrict__ x, const Geometry& geo, const InputMap& mp,
                                              uint32_t gid, typename InRun<Elem, VEC>::Bits (&d)[TT][TT]) {
     constexpr int ES = static_cast<int>(sizeof(Elem));
@@ -166,13 +172,13 @@ __device__ __forceinline__ void input_window(const Elem* __restrict__ x, const G
     const int tx = static_cast<int>(tile - row * mp.tw.d);
     const uint32_t n = fast_div(row, mp.th);
     const int ty = static_cast<int>(row - n * mp.th.d);
-    const int H = mp.h, W = static_cast<int>(geo.W), C = static_cast<int>(geo.C);
+    const int H = static_cast<int>(geo.H), W = static_cast<int>(geo.W), C = static_cast<int>(geo.C);
     const auto rx = __builtin_amdgcn_make_buffer_rsrc(const_cast<Elem*>(x), static_cast<short>(0),
                                                       static_cast<int>(mp.xbytes), static_cast<int>(kRsrcWord3));
     uint32_t ro[TT], co[TT];
 #pragma unroll
     for (int u = 0; u < TT; ++u) {
-        const int hr = ty * m - mp.up + u;
+        const int hr = ty * m + u - (PART == kInTop ? 1 : 0);
         ro[u] = hr >= 0 && hr < H ? (n * static_cast<uint32_t>(H) + static_cast<uint32_t>(hr)) *
                                         static_cast<uint32_t>(W * C * ES)
                                   : 0x80000000u;
@@ -208,7 +214,7 @@ __device__ __forceinline__ void input_window_big(const Elem* __restrict__ x, con
         }
 }
 
-template <typename Elem, int TT, int ALPHA, class CO, int VEC, int RG, bool BIG, bool RELU>
+template <typename Elem, int TT, int ALPHA, class CO, int VEC, int RG, InputPart PART, bool RELU>
 __device__ __forceinline__ void input_regs_unit(const InputTable& tab, const Elem* __restrict__ x,
                                                 unsigned char* __restrict__ V, const Geometry& geo,
                                                 const InputMap& mp, int64_t bid, int64_t G) {
@@ -225,8 +231,8 @@ __device__ __forceinline__ void input_regs_unit(const InputTable& tab, const Ele
     const int64_t gid = base + threadIdx.x;
     if (gid >= mp.threads) return;
     Bits d[TT][TT];
-    if constexpr (BIG) input_window_big<Elem, TT, VEC>(x, geo, gid, d);
-    else input_window<Elem, TT, VEC>(x, geo, mp, static_cast<uint32_t>(gid), d);
+    if constexpr (PART == kInFar) input_window_big<Elem, TT, VEC>(x, geo, gid, d);
+    else input_window<Elem, TT, VEC, PART>(x, geo, mp, static_cast<uint32_t>(gid), d);
     unsigned char* out = V + base * (VEC * ES);
     const uint32_t lo = threadIdx.x * (VEC * ES);
     if constexpr (RG == 1) {

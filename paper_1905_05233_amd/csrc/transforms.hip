@@ -243,10 +243,10 @@ constexpr int64_t kInFewThreads = int64_t(1) << 15;
 // With more units the short kernel transform stays ahead.
 constexpr int64_t kInFirstUnits = 256;
 
-template <typename Elem, int TT, int ALPHA, class CO, int VEC, int RG, bool BIG, bool RELU>
+template <typename Elem, int TT, int ALPHA, class CO, int VEC, int RG, InputPart PART, bool RELU>
 __global__ __launch_bounds__(kInBlock, (input_waves(TT, RG, sizeof(Elem)))) void input_transform(InputTable tab, const Elem* __restrict__ x,
                                                             unsigned char* __restrict__ V, Geometry geo, InputMap mp) {
-    input_regs_unit<Elem, TT, ALPHA, CO, VEC, RG, BIG, RELU>(tab, x, V, geo, mp, blockIdx.x, gridDim.x);
+    input_regs_unit<Elem, TT, ALPHA, CO, VEC, RG, PART, RELU>(tab, x, V, geo, mp, blockIdx.x, gridDim.x);
 }
 
 // The kernel and input transforms are independent: conv2d runs them as one
@@ -270,7 +270,7 @@ __global__ __launch_bounds__(kInBlock) void kernel_input_transform(
         else kernel_transform_run<Elem, ALPHA, 4, false>(ktab, w, U, geo.K, geo.C, geo.Cp, kmp, gid);
         return;
     }
-    input_regs_unit<Elem, TT, ALPHA, CO, VEC, RG, false, RELU>(itab, x, V, geo, mp, bid < n_first ? bid : bid - n_kt, gridDim.x - n_kt);
+    input_regs_unit<Elem, TT, ALPHA, CO, VEC, RG, kInTop, RELU>(itab, x, V, geo, mp, bid < n_first ? bid : bid - n_kt, gridDim.x - n_kt);
 }
 
 // ----------------------------------------------------------------- output
@@ -444,7 +444,6 @@ hipError_t launch_in(const Geometry& g, const KernelTable* ktab, const InputTabl
             mp.th = make_fastdiv(g.th);
             mp.threads = g.T * (g.Cp / vec);
             mp.xbytes = 0;
-            mp.h = mp.up = 0;
             const int64_t blocks = input_blocks(mp.threads, kBigRG);
             if (blocks * kInBlock > kMaxWorkItems) return hipErrorInvalidValue;
             if (ktab) {
@@ -453,7 +452,7 @@ hipError_t launch_in(const Geometry& g, const KernelTable* ktab, const InputTabl
                 if (e != hipSuccess) return e;
             }
 #define WG_IT_BIG(VEC)                                                                                             \
-    hipLaunchKernelGGL((input_transform<Elem, TT, A, CO, VEC, kBigRG, true, false>), dim3(static_cast<unsigned>(blocks)), \
+    hipLaunchKernelGGL((input_transform<Elem, TT, A, CO, VEC, kBigRG, kInFar, false>), dim3(static_cast<unsigned>(blocks)), \
                        dim3(kInBlock), 0, stream, tab, xp, reinterpret_cast<unsigned char*>(vp), g, mp)
             if constexpr (kPairs) {
                 if (pairs) WG_IT_BIG(2);
@@ -473,9 +472,9 @@ hipError_t launch_in(const Geometry& g, const KernelTable* ktab, const InputTabl
         const bool first = n0 == 0 && r0 == 0;
         mp.th = make_fastdiv(nr);
         mp.threads = nn * nr * thr_row;
-        mp.h = static_cast<int>(band.end - band.first);
-        mp.up = static_cast<int>(band.first - r0 * kM + 1);   // 1 at the top of an image, else 0
-        mp.xbytes = static_cast<uint32_t>(nn * mp.h * row * ES);
+        Geometry part = g;
+        part.H = band.end - band.first;
+        mp.xbytes = static_cast<uint32_t>(nn * part.H * row * ES);
         const Elem* xs = xp + n0 * x_img + band.first * row;
         auto* vs = reinterpret_cast<unsigned char*>(vp) + (n0 * tiles_img + r0 * g.tw) * g.Cp * ES;
         const bool split = kBigRG > 1 || (kRG > 1 && mp.threads <= kInFewThreads);
@@ -499,7 +498,7 @@ hipError_t launch_in(const Geometry& g, const KernelTable* ktab, const InputTabl
             const int whole = g.C % (16 / ES) == 0 ? 1 : 0;
 #define WG_KIT(VEC, RG)                                                                                           \
     hipLaunchKernelGGL((kernel_input_transform<Elem, TT, A, CO, VEC, RG, RELU>), grid, dim3(kInBlock), 0, stream, *ktab, \
-                       tab, wp, xs, up, vs, g, mp, kmp, n_kt, n_first, kt_rows, whole)
+                       tab, wp, xs, up, vs, part, mp, kmp, n_kt, n_first, kt_rows, whole)
             if constexpr (kPairs) {
                 if (pairs) WG_KIT(2, 1);
                 else WG_KIT(1, 1);
@@ -511,8 +510,15 @@ hipError_t launch_in(const Geometry& g, const KernelTable* ktab, const InputTabl
         } else {
             if (units > 0x7fffffff) return hipErrorInvalidValue;
             const dim3 grid(static_cast<unsigned>(units));
-#define WG_IT(VEC, RG) \
-    hipLaunchKernelGGL((input_transform<Elem, TT, A, CO, VEC, RG, false, RELU>), grid, dim3(kInBlock), 0, stream, tab, xs, vs, g, mp)
+#define WG_IT(VEC, RG)                                                                                             \
+    do {                                                                                                           \
+        if (r0 == 0)                                                                                               \
+            hipLaunchKernelGGL((input_transform<Elem, TT, A, CO, VEC, RG, kInTop, RELU>), grid, dim3(kInBlock), 0, \
+                               stream, tab, xs, vs, part, mp);                                                     \
+        else if constexpr (!RELU)                                                                                  \
+            hipLaunchKernelGGL((input_transform<Elem, TT, A, CO, VEC, RG, kInBelow, false>), grid, dim3(kInBlock), \
+                               0, stream, tab, xs, vs, part, mp);                                                  \
+    } while (0)
             if constexpr (kPairs) {
                 if (pairs) WG_IT(2, 1);
                 else WG_IT(1, 1);
