@@ -590,6 +590,9 @@ struct Layout1d {
     size_t u_off, v_off, m_off, total;
 };
 
+// V and M are counted also for layers that the one kernel takes, which leaves them
+// untouched: a workspace sized for a layer then serves every smaller one, and
+// smaller ones may take the separate kernels (8x512, 512 -> 512 beside 32x512).
 Layout1d layout_1d(const wg_plan_s* p, int64_t N, int64_t L, int64_t C, int64_t K) {
     Layout1d o;
     o.g = wg::make_geometry_1d(N, L, C, K, p->tr.m, p->tr.alpha);

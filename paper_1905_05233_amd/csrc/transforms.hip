@@ -219,12 +219,12 @@ template <typename Elem> constexpr bool input_pairs(int tt) { return sizeof(Elem
 // scalar registers, and the code (60 KB for the latter, 120 - 266 KB for the
 // others) the instruction cache; a group's part of it fits.  221 thousand threads
 // in bf16, all rows -> split: t = 10, alpha' = 12 64 -> 39 us; 12, 13 126 -> 84;
-// 12, 15 164 -> 88; 14, 14 228 -> 109; 14, 16 334 -> 135.  The others have at most
+// 12, 15 164 -> 87; 14, 14 285 -> 103; 14, 16 334 -> 139.  The others have at most
 // 39 KB, and lose: 12x12 with alpha' = 12 49 -> 55, 10x10 with alpha' = 13 41 -> 64.
 //
 // 14x14 windows in 16 bits take two rows a group up to alpha' = 15: with four the
 // window and the rows' sums need 320 registers, one wave per SIMD (221 thousand
-// threads, alpha' = 14: four rows 132 us, two 109; alpha' = 16: 135 and 145).  Those
+// threads, alpha' = 14: four rows 132 us, two 103; alpha' = 16: 139 and 145).  Those
 // and the fp32 ones come within a few registers of two waves per SIMD, so they are
 // held to it.
 constexpr int kInGroups = 4;
