@@ -93,7 +93,7 @@ def test_every_instance_waits_for_its_products(asm):
     assert not early, early
 
 
-def test_checker_sees_a_missing_wait(asm):
+def test_a_missing_wait_is_seen(asm):
     """With the nops taken out of the text the products' results are read too early."""
     code = next(iter(_kernels(asm).values()))
     assert not _early(code)
